@@ -154,10 +154,9 @@ int make_params(float r_cut, float eps, const float* poly, PairParams* P) {
 
 struct Layout {
     size_t keys_a, vals_a, keys_b, vals_b, counts, hist, scan_tmp, rec,
-        gsorted, cell_items, items, items_sorted, bucket_of, buckets,
-        cell_window, col_cost, col_xcd;
+        gsorted, items, work_ctl, cell_window, col_cost, col_xcd;
     // RCB fat leaves only
-    size_t leafmark, leafidx, leaf_start, leaf_items, cell_list, rcb_counters;
+    size_t leafmark, leafidx, leaf_start, cell_list, rcb_counters;
     bool rcb;
     size_t total;
     int64_t ncell;
@@ -169,8 +168,15 @@ struct Layout {
 
 size_t align_up(size_t v) { return (v + 255) & ~(size_t)255; }
 
-// Work items of the RCB work list: a leaf of c particles gives floor(c / 64)
-// full items and at most two more, and there are at most n leaves.
+// Work items of n targets in `units` non-empty runs of cells or leaves: a unit
+// of c targets gives floor(c / 64) full items and at most two more, splitting
+// adds at most kMaxSplitItems, and every item has a target.
+int item_bound(int64_t units, int64_t n) {
+    return (int)std::max<int64_t>(
+        1, std::min(n, 2 * units + n / kItemI + 1 + kMaxSplitItems));
+}
+
+// Unsplit items of the RCB work list: at most n leaves.
 int64_t rcb_item_bound(int64_t n) { return 2 * n + n / kItemI + 1; }
 
 Layout layout_for(int64_t n, const Geom& g, bool rcb = false) {
@@ -178,9 +184,7 @@ Layout layout_for(int64_t n, const Geom& g, bool rcb = false) {
     const int nn = (int)n;
     L.rcb = rcb;
     L.ncell = (int64_t)g.N * g.N * g.N;
-    // a cell of c targets gives floor(c / 64) full items and at most two more
-    L.max_items = (int)(2 * std::min<int64_t>(n, L.ncell) + n / kItemI + 1);
-    if (rcb) L.max_items = (int)std::max<int64_t>(L.max_items, rcb_item_bound(n));
+    L.max_items = item_bound(rcb ? n : std::min<int64_t>(n, L.ncell), n);
     L.radix_nb = radix_blocks(nn > 0 ? nn : 1);
     // at most three stable passes: digits of ceil(bits / 3) bits, 8 to 11
     const int bits = key_bits(L.ncell) + g.sbits;
@@ -207,11 +211,8 @@ Layout layout_for(int64_t n, const Geom& g, bool rcb = false) {
     // also holds the records in input order during binning (the sorted
     // cotangents are gathered only after the records)
     L.gsorted = take(sizeof(float4) * (size_t)std::max<int64_t>(n, 1));
-    L.cell_items = take(sizeof(int) * (size_t)(L.ncell + 1));
     L.items = take(sizeof(WorkItem) * (size_t)L.max_items);
-    L.items_sorted = take(sizeof(WorkItem) * (size_t)L.max_items);
-    L.bucket_of = take(sizeof(int) * (size_t)L.max_items);
-    L.buckets = take(sizeof(int) * kOrderInts);
+    L.work_ctl = take(sizeof(WorkControl));
     L.cell_window = take(sizeof(int) * (size_t)L.ncell);
     L.col_cost = take(sizeof(unsigned long long) * (size_t)(g.N) * (size_t)g.N);
     L.col_xcd = take(sizeof(int) * (size_t)(g.N) * (size_t)g.N);
@@ -220,7 +221,6 @@ Layout layout_for(int64_t n, const Geom& g, bool rcb = false) {
         L.leafmark = take(n2);
         L.leafidx = take(n2);
         L.leaf_start = take(n2);
-        L.leaf_items = take(n2);
         L.cell_list = take(sizeof(int) * (size_t)L.ncell);
         L.rcb_counters = take(sizeof(int) * 4);
     }
@@ -294,6 +294,11 @@ int rcb_impl(int64_t n, const Geom& g, const Layout& L, const int* cell_start,
     return HACC_SR_OK;
 }
 
+WorkBuffers work_buffers(const Layout& L) {
+    return WorkBuffers{ws_at<WorkControl>(L.work_ctl), ws_at<int>(L.cell_window),
+                       ws_at<unsigned long long>(L.col_cost), ws_at<int>(L.col_xcd)};
+}
+
 // Work list of the RCB leaves, cost-ordered like the chaining-mesh one.
 // Reads the number of leaves back to the host (one stream synchronisation)
 // to size the launch.
@@ -305,24 +310,15 @@ int worklist_rcb_impl(int64_t n, const int* cell_start, const int* keys_sorted,
     HIP_TRY(hipMemcpyAsync(&nleaves, n_leaves_dev, sizeof(int), hipMemcpyDeviceToHost,
                            g_stream));
     HIP_TRY(hipStreamSynchronize(g_stream));
-    int* li = ws_at<int>(L.leaf_items);
+    const int bound = item_bound(nleaves, n);
     WorkItem* items = ws_at<WorkItem>(L.items);
-    WorkItem* sorted = ws_at<WorkItem>(L.items_sorted);
-    int* tmp = ws_at<int>(L.scan_tmp);
-    HIP_TRY(launch_leaf_items(ws_at<int>(L.leaf_start), n_leaves_dev, nleaves, keys_sorted,
-                              g.sbits, li, tmp, items, g_stream));
-    const int64_t bound = n / kItemI + 2 * (int64_t)nleaves + 1;
-    // cell windows and the XCD of each column of cells, for the cost order
-    int* cw = ws_at<int>(L.cell_window);
-    int* cx = ws_at<int>(L.col_xcd);
-    HIP_TRY(launch_items_count(cell_start, g, ws_at<int>(L.cell_items), cw,
-                               ws_at<unsigned long long>(L.col_cost), cx, g_stream));
-    HIP_TRY(launch_items_order(items, li + nleaves, (int)bound, cw, cx, g,
-                               ws_at<int>(L.bucket_of), ws_at<int>(L.buckets), sorted,
-                               g_stream));
-    *items_out = sorted;
-    *n_items_dev = li + nleaves;
-    *grid_items = (int)bound;
+    const WorkBuffers b = work_buffers(L);
+    HIP_TRY(launch_worklist_leaves(cell_start, ws_at<int>(L.leaf_start), n_leaves_dev,
+                                   nleaves, keys_sorted, (int)n, g, bound, b, items,
+                                   g_stream));
+    *items_out = items;
+    *n_items_dev = &b.ctl->n_items;
+    *grid_items = bound;
     return HACC_SR_OK;
 }
 
@@ -332,27 +328,13 @@ int check_leaf_max(int32_t leaf_max) {
 
 
 // Builds the cost-ordered work list; returns the device counter of items.
-int worklist_impl(const int* cell_start, const Geom& g, const Layout& L,
+int worklist_impl(const int* cell_start, int64_t n, const Geom& g, const Layout& L,
                   const WorkItem** items_out, const int** n_items_dev) {
-    int* ci = ws_at<int>(L.cell_items);
     WorkItem* items = ws_at<WorkItem>(L.items);
-    WorkItem* sorted = ws_at<WorkItem>(L.items_sorted);
-    int* bof = ws_at<int>(L.bucket_of);
-    int* bc = ws_at<int>(L.buckets);
-    int* tmp = ws_at<int>(L.scan_tmp);
-    const int nc = (int)L.ncell;
-    HIP_TRY(launch_fill_i32(ci + nc, 1, 0, g_stream));
-    int* cw = ws_at<int>(L.cell_window);
-    int* cx = ws_at<int>(L.col_xcd);
-    HIP_TRY(launch_items_count(cell_start, g, ci, cw,
-                               ws_at<unsigned long long>(L.col_cost), cx,
-                               g_stream));
-    HIP_TRY(launch_scan_exclusive(ci, ci, nc + 1, tmp, g_stream));
-    HIP_TRY(launch_items_write(cell_start, g, ci, items, g_stream));
-    HIP_TRY(launch_items_order(items, ci + nc, L.max_items, cw, cx, g, bof, bc,
-                               sorted, g_stream));
-    *items_out = sorted;
-    *n_items_dev = ci + nc;
+    const WorkBuffers b = work_buffers(L);
+    HIP_TRY(launch_worklist(cell_start, (int)n, g, L.max_items, b, items, g_stream));
+    *items_out = items;
+    *n_items_dev = &b.ctl->n_items;
     return HACC_SR_OK;
 }
 
@@ -404,7 +386,7 @@ int force_into(const double* pos, const float* mass, int64_t n, const Geom& g,
     if (rc != HACC_SR_OK) return rc;
     const WorkItem* items;
     const int* nitems;
-    rc = timed(3, [&] { return worklist_impl(cs, g, L, &items, &nitems); });
+    rc = timed(3, [&] { return worklist_impl(cs, n, g, L, &items, &nitems); });
     if (rc != HACC_SR_OK) return rc;
     if (perm_out) *perm_out = perm;
     return timed(0, [&] {
@@ -483,7 +465,7 @@ int hacc_sr_force_noalloc(const double* pos, const float* mass, int64_t n, doubl
     if ((rc = bin_impl(pos, mass, n, g, L, cs, &perm, rec, nullptr)) != HACC_SR_OK) return rc;
     const WorkItem* items;
     const int* nitems;
-    if ((rc = worklist_impl(cs, g, L, &items, &nitems)) != HACC_SR_OK) return rc;
+    if ((rc = worklist_impl(cs, n, g, L, &items, &nitems)) != HACC_SR_OK) return rc;
     HIP_TRY(launch_pair_force(items, L.max_items, nitems, rec, cs, perm, g, P, out_acc,
                               g_stream));
     return HACC_SR_OK;
@@ -648,7 +630,7 @@ int hacc_sr_force_vjp(const double* pos, const float* mass, int64_t n,
     if (rc != HACC_SR_OK) return rc;
     const WorkItem* items;
     const int* nitems;
-    rc = timed(3, [&] { return worklist_impl(cs, g, L, &items, &nitems); });
+    rc = timed(3, [&] { return worklist_impl(cs, n, g, L, &items, &nitems); });
     if (rc != HACC_SR_OK) return rc;
     rc = timed(1, [&] {
         HIP_TRY(launch_pair_vjp(items, L.max_items, nitems, rec, gs, cs, perm, g,
@@ -684,8 +666,8 @@ int hacc_sr_force_vjp_binned(uint64_t token, int64_t n, double box, float r_cut,
     float4* rec = ws_at<float4>(L.rec);
     float4* gs = ws_at<float4>(L.gsorted);
     int* perm = g_kept.perm;
-    const WorkItem* items = ws_at<WorkItem>(L.items_sorted);
-    const int* nitems = ws_at<int>(L.cell_items) + L.ncell;
+    const WorkItem* items = ws_at<WorkItem>(L.items);
+    const int* nitems = &ws_at<WorkControl>(L.work_ctl)->n_items;
     rc = timed(2, [&] {
         HIP_TRY(launch_gather_vec3(grad_acc, perm, (int)n, gs, g_stream));
         return HACC_SR_OK;
@@ -945,7 +927,7 @@ int hacc_sr_count_pairs(const double* pos, int64_t n, double box, float r_cut,
     if (rc != HACC_SR_OK) return rc;
     const WorkItem* items;
     const int* nitems;
-    if ((rc = worklist_impl(cs, g, L, &items, &nitems)) != HACC_SR_OK) return rc;
+    if ((rc = worklist_impl(cs, n, g, L, &items, &nitems)) != HACC_SR_OK) return rc;
     HIP_TRY(launch_pair_count(items, L.max_items, nitems, rec, cs, g, P,
                               reinterpret_cast<unsigned long long*>(out_counts),
                               g_stream));

@@ -77,20 +77,34 @@ hipError_t launch_fill_i32(int* p, int n, int value, hipStream_t st);
 // work list (worklist.hip)
 constexpr int kCostBuckets = 128;
 constexpr int kXcds = 8;            // XCDs of an MI355X
-// Ints of the ordering buffer: counts and offsets of kXcds * kCostBuckets
-// buckets, then 2 kXcds + 1 list-layout entries.
-constexpr int kOrderInts = 2 * kXcds * kCostBuckets + 2 * kXcds + 1;
-hipError_t launch_items_count(const int* cell_start, Geom g, int* cell_items,
-                              int* cell_window, unsigned long long* col_cost,
-                              int* col_xcd, hipStream_t st);
-hipError_t launch_items_write(const int* cell_start, Geom g,
-                              const int* cell_off, WorkItem* items,
-                              hipStream_t st);
-hipError_t launch_items_order(const WorkItem* items, const int* n_items_dev,
-                              int max_items, const int* cell_window,
-                              const int* col_xcd, Geom g, int* bucket_of,
-                              int* buckets, WorkItem* items_sorted,
-                              hipStream_t st);
+// Item splitting (item_limit): waves the chip holds at 8 per SIMD, and the
+// number of steps below which an item is not split.
+constexpr int kResidentWaves = 8192;
+constexpr int kMinSteps = 256;
+// Items that splitting may add (the bound is in item_limit).
+constexpr int kMaxSplitItems = 2 * kResidentWaves;
+
+struct WorkControl {
+    unsigned long long pairs;             // pair work of all units
+    int n_items;
+    int pad;
+    int count[kXcds * kCostBuckets];      // items per (list, cost bucket)
+    int taken[kXcds * kCostBuckets];      // ranks handed out to blocks
+};
+
+struct WorkBuffers {
+    WorkControl* ctl;
+    int* cell_window;
+    unsigned long long* col_cost;
+    int* col_xcd;
+};
+
+hipError_t launch_worklist(const int* cell_start, int n, Geom g, int max_items,
+                           const WorkBuffers& b, WorkItem* items, hipStream_t st);
+hipError_t launch_worklist_leaves(const int* cell_start, const int* leaf_start,
+                                  const int* n_leaves_dev, int n_leaves,
+                                  const int* keys_sorted, int n, Geom g, int max_items,
+                                  const WorkBuffers& b, WorkItem* items, hipStream_t st);
 
 // pair kernels (pair.hip)
 hipError_t launch_pair_force(const WorkItem* items, int max_items,
@@ -114,10 +128,6 @@ hipError_t launch_rcb(const int* cell_start, int ncell, int n, int leaf_max,
                       int4* nodes, float* split, hipStream_t st);
 hipError_t launch_leaf_table(const int* leafmark, int* leafidx, int n, int* scan_tmp,
                              int* leaf_start, hipStream_t st);
-hipError_t launch_leaf_items(const int* leaf_start, const int* n_leaves_dev,
-                             int max_leaves, const int* keys_sorted, int sbits,
-                             int* leaf_items, int* scan_tmp, WorkItem* items,
-                             hipStream_t st);
 
 // plain reference kernels (plain.hip)
 hipError_t launch_force_plain(const float4* rec, const int* keys_sorted,

@@ -243,62 +243,6 @@ __global__ __launch_bounds__(kRB) void k_leaf_compact(const int* __restrict__ le
     if (i == n) leaf_start[leafidx[n]] = n;
 }
 
-__device__ __forceinline__ int floor_pow2_r(int v) {
-    return v <= 0 ? 0 : (1 << (31 - __clz(v)));
-}
-
-// Items of a leaf of c particles: floor(c / 64) full ones, then at most two
-// for the remainder (the largest power of two, then the rest), as for the
-// cells of the chaining-mesh work list.
-template <typename Emit>
-__device__ void for_leaf_items(int c, Emit emit) {
-    int o = 0;
-    for (; o + kItemI <= c; o += kItemI) emit(o, kItemI, 1);
-    int r = c - o;
-    if (r > 0) {
-        const int p = floor_pow2_r(r);
-        emit(o, p, kItemI / p);
-        o += p;
-        r -= p;
-    }
-    if (r > 0) emit(o, r, floor_pow2_r(kItemI / r));
-}
-
-__global__ __launch_bounds__(kRB) void k_leaf_items_count(
-    const int* __restrict__ leaf_start, const int* __restrict__ n_leaves_dev,
-    int max_leaves, int* __restrict__ leaf_items) {
-    const int l = blockIdx.x * kRB + threadIdx.x;
-    const int nl = *n_leaves_dev;
-    if (l > max_leaves) return;
-    if (l >= nl) {
-        leaf_items[l] = 0;
-        return;
-    }
-    int cnt = 0;
-    for_leaf_items(leaf_start[l + 1] - leaf_start[l], [&](int, int, int) { ++cnt; });
-    leaf_items[l] = cnt;
-}
-
-__global__ __launch_bounds__(kRB) void k_leaf_items_write(
-    const int* __restrict__ leaf_start, const int* __restrict__ n_leaves_dev,
-    const int* __restrict__ item_off, const int* __restrict__ keys_sorted, int sbits,
-    WorkItem* __restrict__ items) {
-    const int l = blockIdx.x * kRB + threadIdx.x;
-    if (l >= *n_leaves_dev) return;
-    const int b = leaf_start[l];
-    const int cell = keys_sorted[b] >> sbits;
-    int k = item_off[l];
-    for_leaf_items(leaf_start[l + 1] - b, [&](int o, int cnt, int ks) {
-        WorkItem it;
-        it.i_begin = b + o;
-        it.i_count = cnt;
-        it.key = cell;
-        it.ksplit = (short)ks;
-        it.zlen = 1;
-        items[k++] = it;
-    });
-}
-
 inline int blocks_for(int64_t n, int per) { return (int)((n + per - 1) / per); }
 
 }  // namespace
@@ -329,20 +273,6 @@ hipError_t launch_leaf_table(const int* leafmark, int* leafidx, int n, int* scan
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_leaf_compact, dim3(blocks_for(n + 1, kRB)), dim3(kRB), 0, st,
                        leafmark, (const int*)leafidx, n, leaf_start);
-    return hipGetLastError();
-}
-
-hipError_t launch_leaf_items(const int* leaf_start, const int* n_leaves_dev,
-                             int max_leaves, const int* keys_sorted, int sbits,
-                             int* leaf_items, int* scan_tmp, WorkItem* items,
-                             hipStream_t st) {
-    hipLaunchKernelGGL(k_leaf_items_count, dim3(blocks_for(max_leaves + 1, kRB)), dim3(kRB),
-                       0, st, leaf_start, n_leaves_dev, max_leaves, leaf_items);
-    hipError_t e = launch_scan_exclusive(leaf_items, leaf_items, max_leaves + 1, scan_tmp, st);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_leaf_items_write, dim3(blocks_for(max_leaves, kRB)), dim3(kRB), 0,
-                       st, leaf_start, n_leaves_dev, (const int*)leaf_items, keys_sorted,
-                       sbits, items);
     return hipGetLastError();
 }
 
