@@ -164,6 +164,7 @@ struct Layout {
     int radix_nb;
     int digit_bits;   // radix digit width (8..11)
     int passes;       // radix passes over the sort key
+    int count_sub;    // counting sort: sub-cell bits of its buckets; -1: radix
 };
 
 size_t align_up(size_t v) { return (v + 255) & ~(size_t)255; }
@@ -179,6 +180,15 @@ int item_bound(int64_t units, int64_t n) {
 // Unsplit items of the RCB work list: at most n leaves.
 int64_t rcb_item_bound(int64_t n) { return 2 * n + n / kItemI + 1; }
 
+// Counting sort of small sets: its buckets are cells, or their 2^3 or 4^3
+// sub-cells as long as that makes at most four per particle.
+int counting_sub_bits(int64_t n, int64_t ncell, int sbits) {
+    if (n > kCountingParticles) return -1;
+    int sub = 0;
+    while (sub + 3 <= sbits && (ncell << (sub + 3)) <= 4 * n) sub += 3;
+    return sub;
+}
+
 Layout layout_for(int64_t n, const Geom& g, bool rcb = false) {
     Layout L{};
     const int nn = (int)n;
@@ -190,7 +200,10 @@ Layout layout_for(int64_t n, const Geom& g, bool rcb = false) {
     const int bits = key_bits(L.ncell) + g.sbits;
     L.digit_bits = std::min(kMaxDigitBits, std::max(8, (bits + 2) / 3));
     L.passes = (bits + L.digit_bits - 1) / L.digit_bits;
-    const int64_t hist_n = ((int64_t)1 << L.digit_bits) * L.radix_nb;
+    int64_t hist_n = ((int64_t)1 << L.digit_bits) * L.radix_nb;
+    L.count_sub = counting_sub_bits(n, L.ncell, g.sbits);
+    if (L.count_sub > 0)
+        hist_n = std::max(hist_n, (L.ncell << L.count_sub) + 1);
     int64_t scan_n = std::max<int64_t>(hist_n, L.ncell + 1);
     if (rcb) scan_n = std::max<int64_t>(scan_n, n + 2);
     size_t off = 0;
@@ -254,6 +267,23 @@ int bin_impl(const double* pos, const float* mass, int64_t n, const Geom& g,
     int* tmp = ws_at<int>(L.scan_tmp);
     float4* rec_in = ws_at<float4>(L.gsorted);
     const int ncp = (int)(L.ncell + 1);
+    if (L.count_sub >= 0) {
+        // keys_a: keys in input order; keys_b: order of arrival, then free;
+        // vals_a: place of arrival, then the sorted keys; vals_b: permutation
+        HIP_TRY(launch_counting_sort(pos, mass, nn, g, L.count_sub, ka, va, rec_in,
+                                     L.count_sub ? hist : cell_start, cell_start, tmp,
+                                     reinterpret_cast<unsigned*>(kb), rec, vb, va, g_stream));
+        std::swap(va, vb);
+        std::swap(ka, vb);
+        if (perm_user) {
+            HIP_TRY(hipMemcpyAsync(perm_user, va, sizeof(int) * (size_t)nn,
+                                   hipMemcpyDeviceToDevice, g_stream));
+        }
+        *perm_out = va;
+        if (keys_out) *keys_out = ka;
+        if (spare_out) *spare_out = vb;
+        return HACC_SR_OK;
+    }
     HIP_TRY(launch_cell_keys(pos, mass, nn, g, ka, va, rec_in, g_stream));
     for (int p = 0; p < L.passes; ++p) {
         HIP_TRY(launch_radix_pass(ka, va, kb, vb, nn, L.digit_bits * p,

@@ -1,4 +1,6 @@
-// Chaining-mesh binning: cell keys and cell-relative float32 records,
+// Chaining-mesh binning: cell keys and cell-relative float32 records, then
+// for small sets a counting sort over the cells (its own section below), for
+// larger ones
 // stable LSD radix passes (each block orders its tile of keys in LDS and
 // writes each digit's keys out as one run), the occupancy histogram of the
 // sorted keys (wave-aggregated atomics: sorted keys arrive in runs), its
@@ -70,10 +72,12 @@ __device__ __forceinline__ int axis_sub(double xw, int c, const Geom& g, int S) 
 // Sort key (cell index, then the sub-cell Morton code) and the float32
 // record (position relative to the cell's lower corner, mass) of every
 // particle, in input order.
+// counts (counting sort only): vals[i] is then the particle's place, in order
+// of arrival, among those of its bucket key >> drop.
 __global__ __launch_bounds__(kBlock) void k_cell_keys(
     const double* __restrict__ pos, const float* __restrict__ mass, int n,
     Geom g, int* __restrict__ keys, int* __restrict__ vals,
-    float4* __restrict__ rec) {
+    float4* __restrict__ rec, int* __restrict__ counts, int drop) {
     const int i = blockIdx.x * kBlock + threadIdx.x;
     if (i >= n) return;
     double xw, yw, zw;
@@ -92,8 +96,9 @@ __global__ __launch_bounds__(kBlock) void k_cell_keys(
             code |= (((sx >> b) & 1) << (3 * b + 2)) |
                     (((sy >> b) & 1) << (3 * b + 1)) | (((sz >> b) & 1) << (3 * b));
     }
-    keys[i] = (key << g.sbits) | code;
-    vals[i] = i;
+    const int full = (key << g.sbits) | code;
+    keys[i] = full;
+    vals[i] = counts ? atomicAdd(&counts[full >> drop], 1) : i;
     float4 r;
     r.x = (float)(xw - (double)cx * g.Lc);
     r.y = (float)(yw - (double)cy * g.Lc);
@@ -191,8 +196,13 @@ __global__ __launch_bounds__(kBlock) void k_scan_single(int* __restrict__ a,
     }
 }
 
+// Scan of one tile plus its carry: bsum[block] when the block sums have been
+// scanned, else the sum of the blocks before it, which the block adds up
+// itself.  With `every`, the scan at each 2^every-th entry also goes to
+// `heads` (the cells' starts among those of their sub-cells).
 __global__ __launch_bounds__(kBlock) void k_scan_apply(
-    const int* in, int* out, int n, const int* __restrict__ bsum) {
+    const int* in, int* out, int n, const int* __restrict__ bsum, bool scanned,
+    int* __restrict__ heads, int every) {
     const int64_t b = (int64_t)blockIdx.x * kTile + (int64_t)threadIdx.x * kItems;
     int v[kItems];
     int s = 0;
@@ -201,11 +211,21 @@ __global__ __launch_bounds__(kBlock) void k_scan_apply(
         v[q] = (b + q < n) ? in[b + q] : 0;
         s += v[q];
     }
-    int tot;
-    int pre = block_excl_scan(s, &tot) + bsum[blockIdx.x];
+    int tot, carry = 0;
+    if (scanned) {
+        carry = bsum[blockIdx.x];
+    } else if (blockIdx.x > 0) {
+        int part = 0;
+        for (int q = threadIdx.x; q < (int)blockIdx.x; q += kBlock) part += bsum[q];
+        block_excl_scan(part, &carry);
+    }
+    int pre = block_excl_scan(s, &tot) + carry;
 #pragma unroll
     for (int q = 0; q < kItems; ++q) {
-        if (b + q < n) out[b + q] = pre;
+        if (b + q < n) {
+            out[b + q] = pre;
+            if (heads && ((b + q) & ((1 << every) - 1)) == 0) heads[(b + q) >> every] = pre;
+        }
         pre += v[q];
     }
 }
@@ -402,6 +422,78 @@ __global__ __launch_bounds__(kBlock) void k_radix_scatter_staged(
     }
 }
 
+// ---------------------------------------------------------------- counting
+// Counting sort for small sets, where the radix passes are a chain of
+// launches that one or a few blocks run (21 launches; 1003 particles 55 us,
+// 65536 107 us): the particles are counted per bucket (a cell, or its
+// sub-cells where cells are well filled) as their keys are formed, placed
+// in their bucket in order of arrival, and each then finds its place by
+// counting the smaller entries of its bucket: sub-cell code, then input
+// index, as the radix sort leaves them.
+
+// Entry of the order array: the key bits below the bucket, then the index.
+constexpr unsigned kIndexMask = (1u << kCountingIndexBits) - 1u;
+
+__global__ __launch_bounds__(kBlock) void k_place(
+    const int* __restrict__ keys, const int* __restrict__ arrival,
+    const int* __restrict__ start, int n, int drop, unsigned* __restrict__ order) {
+    const int i = blockIdx.x * kBlock + threadIdx.x;
+    if (i >= n) return;
+    const int key = keys[i];
+    const unsigned low = (unsigned)key & ((1u << drop) - 1u);
+    order[start[key >> drop] + arrival[i]] = (low << kCountingIndexBits) | (unsigned)i;
+}
+
+// A wave takes 64 consecutive entries.  Their buckets' entries are read 64 at
+// a time, coalesced, and handed round through LDS as broadcast uint4 reads;
+// two instructions per entry where the wave lies in one bucket.
+__global__ __launch_bounds__(kBlock) void k_order_gather(
+    const unsigned* __restrict__ order, const int* __restrict__ start,
+    const int* __restrict__ keys, int n, int drop, const float4* __restrict__ rec_in,
+    float4* __restrict__ rec, int* __restrict__ perm, int* __restrict__ keys_out) {
+    __shared__ __align__(16) unsigned entries[kBlock / kWave][kWave];
+    const int k = blockIdx.x * kBlock + threadIdx.x;
+    const int lane = lane_id(), w = threadIdx.x / kWave;
+    const int k0 = k - lane;                     // the wave's first entry
+    if (k0 >= n) return;
+    const bool live = k < n;
+    const unsigned mine = live ? order[k] : 0u;
+    const int i = (int)(mine & kIndexMask);
+    const int key = keys[i];
+    const int b = start[key >> drop], e = start[(key >> drop) + 1];
+    const int last = min(kWave, n - k0) - 1;
+    const int lo = __shfl(b, 0), hi = __shfl(e, last);
+    const bool one = __ballot(live && (b != lo || e != hi)) == 0ull;
+    unsigned* sh = entries[w];
+    int r = 0;
+    for (int j0 = lo; j0 < hi; j0 += kWave) {
+        const int j = j0 + lane;
+        sh[lane] = j < hi ? order[j] : ~0u;
+        // a wave's LDS accesses complete in program order
+        __builtin_amdgcn_wave_barrier();
+        if (one) {
+#pragma unroll
+            for (int q = 0; q < kWave / 4; ++q) {
+                const unsigned* u = sh + 4 * q;
+                r += (u[0] < mine) + (u[1] < mine) + (u[2] < mine) + (u[3] < mine);
+            }
+        } else {
+#pragma unroll
+            for (int q = 0; q < kWave / 4; ++q) {
+                const unsigned* u = sh + 4 * q;
+                const unsigned at = (unsigned)(j0 + 4 * q - b), len = (unsigned)(e - b);
+                r += (u[0] < mine && at < len) + (u[1] < mine && at + 1u < len) +
+                     (u[2] < mine && at + 2u < len) + (u[3] < mine && at + 3u < len);
+            }
+        }
+        __builtin_amdgcn_wave_barrier();
+    }
+    if (!live) return;
+    rec[b + r] = rec_in[i];
+    perm[b + r] = i;
+    keys_out[b + r] = key;
+}
+
 __global__ __launch_bounds__(kBlock) void k_gather_records(
     const float4* __restrict__ rec_in, const int* __restrict__ perm, int n,
     float4* __restrict__ rec) {
@@ -433,7 +525,7 @@ hipError_t launch_cell_keys(const double* pos, const float* mass, int n,
                             hipStream_t st) {
     if (n <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_cell_keys, dim3(blocks_for(n, kBlock)), dim3(kBlock),
-                       0, st, pos, mass, n, g, keys, vals, rec);
+                       0, st, pos, mass, n, g, keys, vals, rec, (int*)nullptr, 0);
     return hipGetLastError();
 }
 
@@ -447,14 +539,51 @@ hipError_t launch_cell_hist(const int* keys_sorted, int n, int sbits,
 
 size_t scan_tmp_ints(int n) { return (size_t)blocks_for(n, kTile) + 1; }
 
-hipError_t launch_scan_exclusive(const int* in, int* out, int n, int* tmp,
-                                 hipStream_t st) {
+namespace {
+// Block sums that every block of k_scan_apply adds up itself: eight loads per
+// thread at most, less than the launch of k_scan_single.
+constexpr int kOwnCarryBlocks = 2048;
+
+hipError_t scan_exclusive(const int* in, int* out, int n, int* tmp, int* heads, int every,
+                          hipStream_t st) {
     if (n <= 0) return hipSuccess;
     const int nb = blocks_for(n, kTile);
-    hipLaunchKernelGGL(k_scan_reduce, dim3(nb), dim3(kBlock), 0, st, in, n, tmp);
-    hipLaunchKernelGGL(k_scan_single, dim3(1), dim3(kBlock), 0, st, tmp, nb);
+    const bool scanned = nb > kOwnCarryBlocks;
+    if (nb > 1)
+        hipLaunchKernelGGL(k_scan_reduce, dim3(nb), dim3(kBlock), 0, st, in, n, tmp);
+    if (scanned)
+        hipLaunchKernelGGL(k_scan_single, dim3(1), dim3(kBlock), 0, st, tmp, nb);
     hipLaunchKernelGGL(k_scan_apply, dim3(nb), dim3(kBlock), 0, st, in, out, n,
-                       (const int*)tmp);
+                       (const int*)tmp, scanned, heads, every);
+    return hipGetLastError();
+}
+}  // namespace
+
+hipError_t launch_scan_exclusive(const int* in, int* out, int n, int* tmp,
+                                 hipStream_t st) {
+    return scan_exclusive(in, out, n, tmp, nullptr, 0, st);
+}
+
+hipError_t launch_counting_sort(const double* pos, const float* mass, int n, Geom g,
+                                int sub, int* keys, int* arrival, float4* rec_in,
+                                int* buckets, int* cell_start, int* tmp, unsigned* order,
+                                float4* rec, int* perm, int* keys_out, hipStream_t st) {
+    if (n <= 0) return hipSuccess;
+    const int drop = g.sbits - sub;
+    const int nbuckets = (g.N * g.N * g.N) << sub;
+    const dim3 grid(blocks_for(n, kBlock)), block(kBlock);
+    hipError_t e = launch_fill_i32(buckets, nbuckets + 1, 0, st);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_cell_keys, grid, block, 0, st, pos, mass, n, g, keys, arrival,
+                       rec_in, buckets, drop);
+    e = scan_exclusive(buckets, buckets, nbuckets + 1, tmp,
+                       buckets == cell_start ? nullptr : cell_start, sub, st);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_place, grid, block, 0, st, (const int*)keys, (const int*)arrival,
+                       (const int*)buckets, n, drop, order);
+    hipLaunchKernelGGL(k_order_gather, grid, block, 0, st, (const unsigned*)order,
+                       (const int*)buckets, (const int*)keys, n, drop,
+                       (const float4*)rec_in, rec, perm, keys_out);
     return hipGetLastError();
 }
 

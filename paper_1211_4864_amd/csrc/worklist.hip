@@ -170,22 +170,25 @@ __global__ __launch_bounds__(kBlock) void k_windows(
         unsigned long long cost = 0;
         for (int cz = lane; cz < N; cz += kWave) {
             int w = 0;
-            for (int a = -1; a <= 1; ++a)
-                for (int b = -1; b <= 1; ++b) {
-                    int x = cx + a, y = cy + b;
-                    if (g.periodic) {
-                        x = x < 0 ? x + N : (x >= N ? x - N : x);
-                        y = y < 0 ? y + N : (y >= N ? y - N : y);
-                    } else if (x < 0 || x >= N || y < 0 || y >= N) {
-                        continue;
-                    }
-                    const int base = (x * N + y) * N;
-                    w += cs[base + min(cz + 2, N)] - cs[base + max(cz - 1, 0)];
-                    if (g.periodic) {
-                        if (cz == 0) w += cs[base + N] - cs[base + N - 1];
-                        if (cz == N - 1) w += cs[base + 1] - cs[base];
-                    }
+            // the nine columns' loads are independent: all in flight at once
+#pragma unroll
+            for (int q = 0; q < 9; ++q) {
+                int x = cx + q / 3 - 1, y = cy + q % 3 - 1;
+                bool in = true;
+                if (g.periodic) {
+                    x = x < 0 ? x + N : (x >= N ? x - N : x);
+                    y = y < 0 ? y + N : (y >= N ? y - N : y);
+                } else {
+                    in = x >= 0 && x < N && y >= 0 && y < N;
                 }
+                const int base = in ? (x * N + y) * N : 0;
+                int r = cs[base + min(cz + 2, N)] - cs[base + max(cz - 1, 0)];
+                if (g.periodic) {
+                    if (cz == 0) r += cs[base + N] - cs[base + N - 1];
+                    if (cz == N - 1) r += cs[base + 1] - cs[base];
+                }
+                w += in ? r : 0;
+            }
             const int c = col * N + cz;
             cell_window[c] = w;
             // at least the work of the cell's own targets, so that the bound
