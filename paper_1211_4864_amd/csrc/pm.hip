@@ -15,17 +15,18 @@
 // [sin(k D/2) / (k D/2)]^n_s with k = |k|, sigma in grid cells.
 //
 // Layout and order of work (grids complex float32, ng^3 float2, z fastest):
-//  - One pass over the particles writes the grid cell of each particle's
-//    lower CIC corner and a record (the three CIC fractions and the mass,
-//    float32).  The particles are sorted by that cell (a stable LSD radix sort
-//    of the cell index) and their records gathered into that order, so that
-//    the deposit and the interpolation read the records contiguously and
-//    touch the grid locally.
 //  - Deposit: each particle adds m w 2^62 / (n max|m|), rounded to int64, to
-//    its 8 corners.  A wave first sums the contributions of its particles
-//    that share a cell (a segmented scan over the sorted keys), so only one
-//    atomic per cell and wave reaches memory.  Integer sums do not depend on
-//    the order of the additions: the whole solve is bitwise reproducible.
+//    its 8 corners.  Integer sums do not depend on the order of the
+//    additions: the whole solve is bitwise reproducible, and the two ways
+//    below give the same bits.
+//  - Sets whose grid stays in the caches (direct_pm) deposit and interpolate
+//    straight from the positions, one thread per particle in input order.
+//  - Larger sets are sorted by tiles of 8^3 cells first: one pass writes each
+//    particle's lower-corner cell (tile, then cell in the tile) and a record
+//    (the three CIC fractions and the mass, float32), a stable LSD radix sort
+//    orders the tiles, and the records are gathered into that order.  A block
+//    takes kChunk consecutive particles and sums the deposit of each of their
+//    tiles in LDS, so that only its 9^3 sums are added to the grid.
 //  - FFT: one kernel per axis.  A workgroup transforms L lines of ng points
 //    as ng = R1 x R2 (the four-step method): each thread does a length-R1
 //    DFT in registers, multiplies by the twiddles of the length-ng transform
@@ -51,28 +52,59 @@ namespace {
 constexpr int kPB = 256;
 constexpr float kPi = 3.14159265358979323846f;
 
-// ---- mass maximum, for the fixed-point scale
+// ---- preparation
 
 constexpr int kMaxBlocks = 1024;
 
-// Largest |mass| as the bit pattern of a non-negative float (ordered like
-// an unsigned integer): a grid-stride maximum per thread, reduced over the
-// workgroup, one atomic per workgroup.
-__global__ __launch_bounds__(kPB) void k_pm_mass_max(const float* __restrict__ mass, int n,
-                                                     unsigned* __restrict__ out) {
-    __shared__ unsigned part[kPB / kWave];
-    unsigned v = 0u;
-    for (int i = blockIdx.x * kPB + threadIdx.x; i < n; i += gridDim.x * kPB)
-        v = max(v, __float_as_uint(fabsf(mass[i])));
+// Per-axis terms of the symbols at index m (below, with the FFT).
+__device__ __forceinline__ float4 axis_symbol(int m, int ng, float d);
+
+// Block-wide maximum of an unsigned value per thread, in every thread.
+template <int THREADS>
+__device__ __forceinline__ unsigned block_max(unsigned v) {
+    __shared__ unsigned part[THREADS / kWave];
 #pragma unroll
     for (int o = 1; o < kWave; o <<= 1) v = max(v, (unsigned)__shfl_xor((int)v, o));
     if ((threadIdx.x & (kWave - 1)) == 0) part[threadIdx.x / kWave] = v;
     __syncthreads();
-    if (threadIdx.x == 0) {
-        unsigned m = part[0];
-        for (int w = 1; w < kPB / kWave; ++w) m = max(m, part[w]);
-        atomicMax(out, m);
+    v = part[0];
+#pragma unroll
+    for (int w = 1; w < THREADS / kWave; ++w) v = max(v, part[w]);
+    return v;
+}
+
+// Everything the deposit needs, in one launch: clears the fixed-point grid,
+// writes tw[k] = exp(-2 pi i k / ng) and the per-axis symbol terms, and
+// leaves each block's largest |mass| (as the bit pattern of a non-negative
+// float, ordered like an unsigned integer) in mass_max.
+__global__ __launch_bounds__(kPB) void k_pm_prepare(
+    const float* __restrict__ mass, int n, int ng, float d, ulonglong2* __restrict__ grid,
+    float2* __restrict__ tw, float4* __restrict__ sym, unsigned* __restrict__ mass_max) {
+    const int64_t first = (int64_t)blockIdx.x * kPB + threadIdx.x;
+    const int64_t all = (int64_t)gridDim.x * kPB;
+    const int64_t pairs = (int64_t)ng * ng * ng / 2;
+    for (int64_t k = first; k < pairs; k += all) grid[k] = make_ulonglong2(0ull, 0ull);
+    for (int64_t k = first; k < ng; k += all) {
+        float s, c;
+        sincospif(2.0f * (float)k / (float)ng, &s, &c);
+        tw[k] = make_float2(c, -s);
+        sym[k] = axis_symbol((int)k, ng, d);
     }
+    unsigned v = 0u;
+    for (int64_t k = first; k < n; k += all) v = max(v, __float_as_uint(fabsf(mass[k])));
+    v = block_max<kPB>(v);
+    if (threadIdx.x == 0) mass_max[blockIdx.x] = v;
+}
+
+// Largest |mass| of all, from the blocks' maxima; kept in mass_max[kMaxBlocks]
+// for the transform.
+template <int THREADS>
+__device__ __forceinline__ double largest_mass(unsigned* mass_max, int blocks) {
+    unsigned v = 0u;
+    for (int k = threadIdx.x; k < blocks; k += THREADS) v = max(v, mass_max[k]);
+    v = block_max<THREADS>(v);
+    if (blockIdx.x == 0 && threadIdx.x == 0) mass_max[kMaxBlocks] = v;
+    return (double)__uint_as_float(v);
 }
 
 // ---- sort by cell
@@ -97,6 +129,31 @@ __device__ __forceinline__ void cic_point(const double* __restrict__ pos, int i,
     for (int a = 0; a < 3; ++a) g0[a] = cic_axis(pos[3 * (int64_t)i + a], inv_d, ng, &f[a]);
 }
 
+// Tiles of kSide^3 cells: the sort key is the tile's index (x, y, z; z fastest)
+// followed by the cell's in the tile.
+constexpr int kSide = 8;
+constexpr int kSideBits = 3;
+constexpr int kCellBits = 3 * kSideBits;
+
+__device__ __forceinline__ int tile_key(const int g0[3], int ng) {
+    const int nt = ng / kSide;
+    const int tile = ((g0[0] / kSide) * nt + g0[1] / kSide) * nt + g0[2] / kSide;
+    const int cell = ((g0[0] % kSide) * kSide + g0[1] % kSide) * kSide + g0[2] % kSide;
+    return (tile << kCellBits) | cell;
+}
+
+// Lower corner of a key's cell, and of its tile.
+__device__ __forceinline__ void key_corner(int key, int ng, int g0[3], int t0[3]) {
+    const int nt = ng / kSide;
+    const int tile = key >> kCellBits;
+    t0[2] = tile % nt * kSide;
+    t0[1] = tile / nt % nt * kSide;
+    t0[0] = tile / (nt * nt) * kSide;
+    g0[2] = t0[2] + (key & (kSide - 1));
+    g0[1] = t0[1] + ((key >> kSideBits) & (kSide - 1));
+    g0[0] = t0[0] + ((key >> (2 * kSideBits)) & (kSide - 1));
+}
+
 __global__ __launch_bounds__(kPB) void k_pm_keys(const double* __restrict__ pos,
                                                  const float* __restrict__ mass, int n, int ng,
                                                  double inv_d, int* __restrict__ keys,
@@ -107,7 +164,7 @@ __global__ __launch_bounds__(kPB) void k_pm_keys(const double* __restrict__ pos,
     int g0[3];
     double f[3];
     cic_point(pos, i, inv_d, ng, g0, f);
-    keys[i] = (g0[0] * ng + g0[1]) * ng + g0[2];
+    keys[i] = tile_key(g0, ng);
     vals[i] = i;
     rec[i] = make_float4((float)f[0], (float)f[1], (float)f[2], mass[i]);
 }
@@ -118,16 +175,6 @@ __global__ __launch_bounds__(kPB) void k_pm_gather(const int* __restrict__ perm,
     const int k = blockIdx.x * kPB + threadIdx.x;
     if (k >= n) return;
     rec[k] = rec_in[perm[k]];
-}
-
-// Lower corner of a cell key and the fractions of a record.
-__device__ __forceinline__ void cic_record(int key, float4 r, int ng, int g0[3], double f[3]) {
-    g0[2] = key % ng;
-    g0[1] = (key / ng) % ng;
-    g0[0] = key / (ng * ng);
-    f[0] = (double)r.x;
-    f[1] = (double)r.y;
-    f[2] = (double)r.z;
 }
 
 // ---- deposit
@@ -145,53 +192,189 @@ __device__ __forceinline__ double corner_weight(const double f[3], int c) {
     return (bx ? f[0] : 1.0 - f[0]) * (by ? f[1] : 1.0 - f[1]) * (bz ? f[2] : 1.0 - f[2]);
 }
 
-// Lane k of the grid takes the k-th particle in cell order.  Lanes of a wave
-// with the same key form a segment; for each corner a segmented inclusive
-// scan leaves the segment's sum in its last lane, which adds it to the grid.
-__global__ __launch_bounds__(kPB) void k_pm_deposit(const int* __restrict__ keys,
-                                                    const float4* __restrict__ rec, int n,
-                                                    int ng,
-                                                    const unsigned* __restrict__ mmax_bits,
-                                                    unsigned long long* __restrict__ grid) {
-    const double mmax = (double)__uint_as_float(*mmax_bits);
-    if (!(mmax > 0.0)) return;                       // uniform: nothing to deposit
-    const double scale = 4611686018427387904.0 / ((double)n * mmax);   // 2^62
-    const int k = blockIdx.x * kPB + threadIdx.x;
-    const int lane = threadIdx.x & (kWave - 1);
-    const bool live = k < n;
-    const int key = live ? keys[k] : -1 - lane;      // padding lanes: own segments
-    int g0[3] = {0, 0, 0};
-    double f[3] = {0.0, 0.0, 0.0};
-    double m = 0.0;
-    if (live) {
-        const float4 r = rec[k];
-        cic_record(key, r, ng, g0, f);
-        m = (double)r.w * scale;
-    }
-    const int prev = __shfl_up(key, 1);
-    const int next = __shfl_down(key, 1);
-    const bool head = lane == 0 || prev != key;
-    const bool tail = lane == kWave - 1 || next != key;
-    const unsigned long long heads = __ballot(head);
-    if (heads == ~0ull) {                            // no shared cells in this wave
-        if (!live) return;
-        for (int c = 0; c < 8; ++c) {
-            const long long q = llrint(m * corner_weight(f, c));
-            atomicAdd(&grid[corner_index(g0, c, ng)], (unsigned long long)q);
-        }
-        return;
-    }
-    const unsigned long long upto = (2ull << lane) - 1ull;   // lanes 0..lane
-    const int sstart = 63 - __clzll(heads & upto);
-    for (int c = 0; c < 8; ++c) {
-        long long v = live ? llrint(m * corner_weight(f, c)) : 0ll;
+__device__ __forceinline__ void deposit_one(unsigned long long* grid, const int g0[3],
+                                            const double f[3], double m, int ng) {
 #pragma unroll
-        for (int off = 1; off < kWave; off <<= 1) {
-            const long long t = __shfl_up(v, off);
-            if (lane - off >= sstart) v += t;
+    for (int c = 0; c < 8; ++c)
+        atomicAdd(&grid[corner_index(g0, c, ng)],
+                  (unsigned long long)llrint(m * corner_weight(f, c)));
+}
+
+constexpr double kFixedScale = 4611686018427387904.0;      // 2^62
+
+// Particles in input order.  Atomics of many blocks on one address take about
+// 180 ns each in turn, so the dense cells of a clustered set bound this: a
+// block first adds up its particles' corners in an LDS table (an entry
+// belongs to the first corner that claims it; others that meet it go to
+// memory) and adds each entry to the grid once.  50000 Plummer particles on
+// 64^3: 54 us with one atomic per corner, 28 with the table.  The
+// fractions are rounded to float32 as the records of the sorted path hold them.
+constexpr int kDB = 256;                  // threads of a block
+constexpr int kDChunk = 512;              // its particles
+constexpr int kTableBits = 12;
+constexpr int kTable = 1 << kTableBits;   // its table
+
+__global__ __launch_bounds__(kDB) void k_pm_deposit_direct(
+    const double* __restrict__ pos, const float* __restrict__ mass, int n, int ng,
+    double inv_d, unsigned* __restrict__ mass_max, int mass_blocks,
+    unsigned long long* __restrict__ grid) {
+    __shared__ int owner[kTable];
+    __shared__ unsigned long long sum[kTable];
+    for (int v = threadIdx.x; v < kTable; v += kDB) {
+        owner[v] = -1;
+        sum[v] = 0ull;
+    }
+    const double mmax = largest_mass<kDB>(mass_max, mass_blocks);   // synchronises
+    if (!(mmax > 0.0)) return;                       // uniform: nothing to deposit
+    const double scale = kFixedScale / ((double)n * mmax);
+    const int first = blockIdx.x * kDChunk;
+    const int end = min(n, first + kDChunk);
+    for (int i = first + (int)threadIdx.x; i < end; i += kDB) {
+        int g0[3];
+        double f[3];
+        cic_point(pos, i, inv_d, ng, g0, f);
+#pragma unroll
+        for (int a = 0; a < 3; ++a) f[a] = (double)(float)f[a];
+        const double m = (double)mass[i] * scale;
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+            const int at = (int)corner_index(g0, c, ng);
+            const unsigned long long q = (unsigned long long)llrint(m * corner_weight(f, c));
+            const int v = (int)(((unsigned)at * 2654435761u) >> (32 - kTableBits));
+            const int had = atomicCAS(&owner[v], -1, at);
+            if (had == -1 || had == at) atomicAdd(&sum[v], q);
+            else atomicAdd(&grid[at], q);
         }
-        if (tail && live)
-            atomicAdd(&grid[corner_index(g0, c, ng)], (unsigned long long)v);
+    }
+    __syncthreads();
+    for (int v = threadIdx.x; v < kTable; v += kDB)
+        if (owner[v] >= 0 && sum[v]) atomicAdd(&grid[owner[v]], sum[v]);
+}
+
+// Particles of a block of the sorted passes, and the fewest of one tile that
+// the block takes through LDS: below that, clearing and adding (or reading)
+// the tile's 9^3 values costs more than the particles' own 8 corners.
+constexpr int kChunk = 2048;
+constexpr int kFewest = 64;
+constexpr int kEdge = kSide + 1;
+constexpr int kCorners = kEdge * kEdge * kEdge;
+
+// The tiles of a block's particles: the ranges of tiles with at least kFewest
+// of them (in any order), and tile[q] = -1 for the particles of the others.
+struct Ranges {
+    int tile[kChunk];
+    int start[kChunk + 1];
+    int2 full[kChunk / kFewest];
+    int n_full;
+    int part[kPB / kWave];
+};
+
+__device__ __forceinline__ void find_ranges(const int* __restrict__ keys, int first, int m,
+                                            Ranges& r) {
+    constexpr int kPer = kChunk / kPB;
+    for (int q = threadIdx.x; q < m; q += kPB) r.tile[q] = keys[first + q] >> kCellBits;
+    if (threadIdx.x == 0) r.n_full = 0;
+    __syncthreads();
+    // thread t looks at entries t * kPer ..: a scan of the counts of starts
+    // gives each start its place
+    bool is[kPer];
+    int mine = 0;
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+        const int q = threadIdx.x * kPer + j;
+        is[j] = q < m && (q == 0 || r.tile[q] != r.tile[q - 1]);
+        mine += is[j];
+    }
+    const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
+    int incl = mine;
+#pragma unroll
+    for (int d = 1; d < kWave; d <<= 1) {
+        const int o = __shfl_up(incl, d);
+        if (lane >= d) incl += o;
+    }
+    if (lane == kWave - 1) r.part[w] = incl;
+    __syncthreads();
+    int at = incl - mine, all = 0;
+#pragma unroll
+    for (int k = 0; k < kPB / kWave; ++k) {
+        if (k < w) at += r.part[k];
+        all += r.part[k];
+    }
+#pragma unroll
+    for (int j = 0; j < kPer; ++j)
+        if (is[j]) r.start[at++] = threadIdx.x * kPer + j;
+    if (threadIdx.x == 0) r.start[all] = m;
+    __syncthreads();
+    for (int t = threadIdx.x; t < all; t += kPB) {
+        const int a = r.start[t], b = r.start[t + 1];
+        if (b - a >= kFewest)
+            r.full[atomicAdd(&r.n_full, 1)] = make_int2(a, b);
+        else
+            for (int q = a; q < b; ++q) r.tile[q] = -1;
+    }
+    __syncthreads();
+}
+
+// Index of corner c of a cell in its tile's 9^3 corners, and the grid index of
+// corner v of a tile.
+__device__ __forceinline__ int corner_in_tile(int key, int c) {
+    const int x = ((key >> (2 * kSideBits)) & (kSide - 1)) + (c >> 2);
+    const int y = ((key >> kSideBits) & (kSide - 1)) + ((c >> 1) & 1);
+    const int z = (key & (kSide - 1)) + (c & 1);
+    return (x * kEdge + y) * kEdge + z;
+}
+
+__device__ __forceinline__ int64_t tile_corner_index(const int t0[3], int v, int ng) {
+    int x = t0[0] + v / (kEdge * kEdge), y = t0[1] + v / kEdge % kEdge, z = t0[2] + v % kEdge;
+    x = x == ng ? 0 : x;
+    y = y == ng ? 0 : y;
+    z = z == ng ? 0 : z;
+    return ((int64_t)x * ng + y) * ng + z;
+}
+
+// Bound by the LDS atomics (8 of 64 bits per particle); 16.8M NFW particles
+// on 256^3: 0.78 ms with the sums of equal cells formed in registers and every
+// corner added in memory, 0.27 now.
+__global__ __launch_bounds__(kPB) void k_pm_deposit(
+    const int* __restrict__ keys, const float4* __restrict__ rec, int n, int ng,
+    unsigned* __restrict__ mass_max, int mass_blocks,
+    unsigned long long* __restrict__ grid) {
+    __shared__ Ranges r;
+    __shared__ unsigned long long acc[kCorners];
+    const double mmax = largest_mass<kPB>(mass_max, mass_blocks);
+    if (!(mmax > 0.0)) return;                       // uniform: nothing to deposit
+    const double scale = kFixedScale / ((double)n * mmax);
+    const int first = blockIdx.x * kChunk;
+    const int m = min(kChunk, n - first);
+    find_ranges(keys, first, m, r);
+    for (int q = threadIdx.x; q < m; q += kPB) {
+        if (r.tile[q] >= 0) continue;
+        const float4 p = rec[first + q];
+        const double f[3] = {(double)p.x, (double)p.y, (double)p.z};
+        int g0[3], t0[3];
+        key_corner(keys[first + q], ng, g0, t0);
+        deposit_one(grid, g0, f, (double)p.w * scale, ng);
+    }
+    for (int t = 0; t < r.n_full; ++t) {
+        const int a = r.full[t].x, b = r.full[t].y;
+        for (int v = threadIdx.x; v < kCorners; v += kPB) acc[v] = 0ull;
+        __syncthreads();
+        for (int q = a + (int)threadIdx.x; q < b; q += kPB) {
+            const int key = keys[first + q];
+            const float4 p = rec[first + q];
+            const double f[3] = {(double)p.x, (double)p.y, (double)p.z};
+            const double w = (double)p.w * scale;
+#pragma unroll
+            for (int c = 0; c < 8; ++c)
+                atomicAdd(&acc[corner_in_tile(key, c)],
+                          (unsigned long long)llrint(w * corner_weight(f, c)));
+        }
+        __syncthreads();
+        int g0[3], t0[3];
+        key_corner(r.tile[a] << kCellBits, ng, g0, t0);
+        for (int v = threadIdx.x; v < kCorners; v += kPB)
+            if (acc[v]) atomicAdd(&grid[tile_corner_index(t0, v, ng)], acc[v]);
+        __syncthreads();
     }
 }
 
@@ -412,35 +595,16 @@ __global__ __launch_bounds__(kPB) void k_fft(FftArgs A) {
     }
 }
 
-// tw[k] = exp(-2 pi i k / ng) and the per-axis symbol terms, k < ng.
-__global__ __launch_bounds__(kPB) void k_tables(int ng, float d, float2* __restrict__ tw,
-                                                float4* __restrict__ sym) {
-    const int k = blockIdx.x * kPB + threadIdx.x;
-    if (k >= ng) return;
-    float s, c;
-    sincospif(2.0f * (float)k / (float)ng, &s, &c);
-    tw[k] = make_float2(c, -s);
-    sym[k] = axis_symbol(k, ng, d);
-}
-
 // ---- interpolation
 
-// Lane k takes the k-th particle in cell order: a_x, a_y from the real and
-// imaginary parts of grid b, a_z from the real part of grid a.
-__global__ __launch_bounds__(kPB) void k_pm_interp(const int* __restrict__ perm,
-                                                   const int* __restrict__ keys,
-                                                   const float4* __restrict__ rec, int n,
-                                                   int ng,
-                                                   const float2* __restrict__ gxy,
-                                                   const float2* __restrict__ gz,
-                                                   float* __restrict__ out) {
-    const int k = blockIdx.x * kPB + threadIdx.x;
-    if (k >= n) return;
-    const int i = perm[k];
-    int g0[3];
-    double f[3];
-    cic_record(keys[k], rec[k], ng, g0, f);
+// a_x, a_y come from the real and imaginary parts of grid b, a_z from the real
+// part of grid a.
+__device__ __forceinline__ void interp_one(const float2* __restrict__ gxy,
+                                           const float2* __restrict__ gz, const int g0[3],
+                                           const double f[3], int ng,
+                                           float* __restrict__ out) {
     float ax = 0.0f, ay = 0.0f, az = 0.0f;
+#pragma unroll
     for (int c = 0; c < 8; ++c) {
         const float w = (float)corner_weight(f, c);
         const int64_t at = corner_index(g0, c, ng);
@@ -449,9 +613,105 @@ __global__ __launch_bounds__(kPB) void k_pm_interp(const int* __restrict__ perm,
         ay = __builtin_fmaf(w, xy.y, ay);
         az = __builtin_fmaf(w, gz[at].x, az);
     }
-    out[3 * (int64_t)i + 0] = ax;
-    out[3 * (int64_t)i + 1] = ay;
-    out[3 * (int64_t)i + 2] = az;
+    out[0] = ax;
+    out[1] = ay;
+    out[2] = az;
+}
+
+__global__ __launch_bounds__(kPB) void k_pm_interp_direct(
+    const double* __restrict__ pos, int n, int ng, double inv_d,
+    const float2* __restrict__ gxy, const float2* __restrict__ gz, float* __restrict__ out) {
+    const int i = blockIdx.x * kPB + threadIdx.x;
+    if (i >= n) return;
+    int g0[3];
+    double f[3];
+    cic_point(pos, i, inv_d, ng, g0, f);
+#pragma unroll
+    for (int a = 0; a < 3; ++a) f[a] = (double)(float)f[a];
+    interp_one(gxy, gz, g0, f, ng, out + 3 * (int64_t)i);
+}
+
+// A block takes kIChunk particles in tile order, reads the 9^3 corners of each
+// of their tiles into LDS once and interpolates from there; where they lie in
+// more than kMostTiles tiles, reading those in turn takes longer than each
+// particle's own corners do.
+// Bound by the scattered 12-byte writes (0.23 ms of it) and the tiles' corners:
+// 16.8M NFW particles on 256^3 take 0.53 ms, 0.80 with every corner read from
+// memory, 0.56 and 0.66 with 512 and 2048 particles per block (0.46 with
+// every corner from memory after a full sort by cell, whose third radix pass
+// takes 0.16 ms).
+constexpr int kIChunk = 1024;
+constexpr int kMostTiles = 6;
+__global__ __launch_bounds__(kPB) void k_pm_interp(
+    const int* __restrict__ perm, const int* __restrict__ keys,
+    const float4* __restrict__ rec, int n, int ng, const float2* __restrict__ gxy,
+    const float2* __restrict__ gz, float* __restrict__ out) {
+    constexpr int kPer = kIChunk / kPB;
+    __shared__ float4 field[kCorners];
+    __shared__ int next_tile;
+    const int first = blockIdx.x * kIChunk;
+    const int m = min(kIChunk, n - first);
+    int key[kPer], dst[kPer];
+    float4 p[kPer];
+    int tiles = 0;
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+        const int q = j * kPB + (int)threadIdx.x;
+        const int k = first + min(q, m - 1);
+        key[j] = q < m ? keys[k] : -1;
+        p[j] = rec[k];
+        dst[j] = perm[k];
+        tiles += __syncthreads_count(q < m && (q == 0 || keys[k - 1] >> kCellBits !=
+                                                             key[j] >> kCellBits));
+    }
+    if (tiles > kMostTiles) {
+#pragma unroll
+        for (int j = 0; j < kPer; ++j) {
+            if (key[j] < 0) continue;
+            const double f[3] = {(double)p[j].x, (double)p[j].y, (double)p[j].z};
+            int g0[3], t0[3];
+            key_corner(key[j], ng, g0, t0);
+            interp_one(gxy, gz, g0, f, ng, out + 3 * (int64_t)dst[j]);
+        }
+        return;
+    }
+    int tile = keys[first] >> kCellBits;
+    for (int left = tiles; left > 0; --left) {
+        if (threadIdx.x == 0) next_tile = 0x7fffffff;
+        int g0[3], t0[3];
+        key_corner(tile << kCellBits, ng, g0, t0);
+        for (int v = threadIdx.x; v < kCorners; v += kPB) {
+            const int64_t at = tile_corner_index(t0, v, ng);
+            const float2 xy = gxy[at];
+            field[v] = make_float4(xy.x, xy.y, gz[at].x, 0.0f);
+        }
+        __syncthreads();
+        int after = 0x7fffffff;
+#pragma unroll
+        for (int j = 0; j < kPer; ++j) {
+            const int tj = key[j] >> kCellBits;       // -1 for no particle
+            if (tj > tile) after = min(after, tj);
+            if (tj != tile) continue;
+            const double f[3] = {(double)p[j].x, (double)p[j].y, (double)p[j].z};
+            float ax = 0.0f, ay = 0.0f, az = 0.0f;
+#pragma unroll
+            for (int c = 0; c < 8; ++c) {
+                const float w = (float)corner_weight(f, c);
+                const float4 e = field[corner_in_tile(key[j], c)];
+                ax = __builtin_fmaf(w, e.x, ax);
+                ay = __builtin_fmaf(w, e.y, ay);
+                az = __builtin_fmaf(w, e.z, az);
+            }
+            float* o = out + 3 * (int64_t)dst[j];
+            o[0] = ax;
+            o[1] = ay;
+            o[2] = az;
+        }
+        if (after != 0x7fffffff) atomicMin(&next_tile, after);
+        __syncthreads();
+        tile = next_tile;
+        __syncthreads();
+    }
 }
 
 inline int blocks_for(int64_t n, int per) { return (int)((n + per - 1) / per); }
@@ -467,15 +727,22 @@ void launch_fft_all(const FftArgs& a, hipStream_t st) {
     hipLaunchKernelGGL((k_fft<NG, 2, kPlain, +1>), dim3(S::TILES, 2), blk, 0, st, a);
 }
 
-// Radix sort of the cell keys: bits = 3 log2(ng), at most three passes of
-// 8..10-bit digits.
+// Radix sort of the tiles: 3 log2(ng / kSide) bits in passes of 8 or 9.
 void pm_sort_shape(int ng, int* passes, int* digit_bits) {
     int lg = 0;
     while ((1 << lg) < ng) ++lg;
-    const int bits = 3 * lg;
-    const int p = (bits + 9) / 10;
-    *passes = p;
-    *digit_bits = std::max(8, (bits + p - 1) / p);
+    const int bits = 3 * (lg - kSideBits);
+    *passes = (bits + 8) / 9;
+    *digit_bits = *passes ? std::max(8, (bits + *passes - 1) / *passes) : 8;
+}
+
+// Whether to deposit and interpolate in input order, without the sort: its
+// launches cost more than the scattered accesses to a grid (microseconds,
+// direct / sorted, NFW): 32^3 with 32768 particles 42 / 76, with 262144
+// 135 / 89; 64^3 50000 60 / 101, 262144 163 / 111; 128^3 16384 91 / 171,
+// 262144 238 / 215; 256^3 262144 530 / 555, 2097152 1427 / 949.
+bool direct_pm(int ng, int64_t n) {
+    return n <= (1 << 17) + std::min<int64_t>((int64_t)ng * ng * ng / 64, 1 << 18);
 }
 
 struct PmLayout {
@@ -501,7 +768,7 @@ PmLayout pm_layout(int ng, int64_t n) {
     L.b = take(cells * sizeof(float2));      // also the fixed-point deposit
     L.tw = take((size_t)ng * sizeof(float2));
     L.sym = take((size_t)ng * sizeof(float4));
-    L.mmax = take(sizeof(unsigned));
+    L.mmax = take(sizeof(unsigned) * (kMaxBlocks + 1));
     L.keys_a = take(ni);
     L.vals_a = take(ni);
     L.keys_b = take(ni);
@@ -520,6 +787,7 @@ size_t pm_workspace_bytes(int ng, int64_t n) { return pm_layout(ng, n).total; }
 
 hipError_t launch_pm_accel(const double* pos, const float* mass, int n, double box, int ng,
                            float sigma, int n_s, void* ws, float* out_acc, hipStream_t st) {
+    if (n <= 0) return hipSuccess;
     const int64_t cells = (int64_t)ng * ng * ng;
     const PmLayout PL = pm_layout(ng, n);
     char* base = reinterpret_cast<char*>(ws);
@@ -539,29 +807,29 @@ hipError_t launch_pm_accel(const double* pos, const float* mass, int n, double b
     int* tmp = reinterpret_cast<int*>(base + PL.scan_tmp);
     const double d = box / ng;
     const double inv_d = (double)ng / box;
-    hipError_t e = launch_fill_i32(reinterpret_cast<int*>(mmax), 1, 0, st);
-    if (e != hipSuccess) return e;
-    e = launch_fill_i32(reinterpret_cast<int*>(Q), (int)(2 * cells), 0, st);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_tables, dim3(blocks_for(ng, kPB)), dim3(kPB), 0, st, ng, (float)d,
-                       tw, sym);
-    if (n > 0) {
-        hipLaunchKernelGGL(k_pm_mass_max, dim3(std::min(kMaxBlocks, blocks_for(n, kPB))),
-                           dim3(kPB), 0, st, mass, n, mmax);
+    const int mb = std::min(kMaxBlocks, std::max(blocks_for(n, kPB), blocks_for(cells / 2, kPB)));
+    hipLaunchKernelGGL(k_pm_prepare, dim3(mb), dim3(kPB), 0, st, mass, n, ng, (float)d,
+                       reinterpret_cast<ulonglong2*>(Q), tw, sym, mmax);
+    const bool direct = direct_pm(ng, n);
+    if (direct) {
+        hipLaunchKernelGGL(k_pm_deposit_direct, dim3(blocks_for(n, kDChunk)), dim3(kDB), 0, st, pos,
+                           mass, n, ng, inv_d, mmax, mb, Q);
+    } else {
         hipLaunchKernelGGL(k_pm_keys, dim3(blocks_for(n, kPB)), dim3(kPB), 0, st, pos, mass,
                            n, ng, inv_d, ka, va, rec_in);
         int passes, db;
         pm_sort_shape(ng, &passes, &db);
         for (int p = 0; p < passes; ++p) {
-            e = launch_radix_pass(ka, va, kb, vb, n, db * p, db, hist, tmp, st);
+            const hipError_t e = launch_radix_pass(ka, va, kb, vb, n, kCellBits + db * p, db,
+                                                   hist, tmp, st);
             if (e != hipSuccess) return e;
             std::swap(ka, kb);
             std::swap(va, vb);
         }
         hipLaunchKernelGGL(k_pm_gather, dim3(blocks_for(n, kPB)), dim3(kPB), 0, st,
                            (const int*)va, (const float4*)rec_in, n, rec);
-        hipLaunchKernelGGL(k_pm_deposit, dim3(blocks_for(n, kPB)), dim3(kPB), 0, st,
-                           (const int*)ka, (const float4*)rec, n, ng, (const unsigned*)mmax, Q);
+        hipLaunchKernelGGL(k_pm_deposit, dim3(blocks_for(n, kChunk)), dim3(kPB), 0, st,
+                           (const int*)ka, (const float4*)rec, n, ng, mmax, mb, Q);
     }
     FftArgs fa{};
     fa.a = A;
@@ -569,7 +837,7 @@ hipError_t launch_pm_accel(const double* pos, const float* mass, int n, double b
     fa.q = Q;
     fa.tw = tw;
     fa.sym = sym;
-    fa.mmax_bits = mmax;
+    fa.mmax_bits = mmax + kMaxBlocks;
     // density = q (n max|m| / 2^62) / D^3; k_fft multiplies by max|m|
     fa.unit = (double)n / 4611686018427387904.0 / (d * d * d);
     fa.d = (float)d;
@@ -585,8 +853,11 @@ hipError_t launch_pm_accel(const double* pos, const float* mass, int n, double b
         case 512: launch_fft_all<512>(fa, st); break;
         default: return hipErrorInvalidValue;
     }
-    if (n > 0)
-        hipLaunchKernelGGL(k_pm_interp, dim3(blocks_for(n, kPB)), dim3(kPB), 0, st,
+    if (direct)
+        hipLaunchKernelGGL(k_pm_interp_direct, dim3(blocks_for(n, kPB)), dim3(kPB), 0, st, pos,
+                           n, ng, inv_d, (const float2*)B, (const float2*)A, out_acc);
+    else
+        hipLaunchKernelGGL(k_pm_interp, dim3(blocks_for(n, kIChunk)), dim3(kPB), 0, st,
                            (const int*)va, (const int*)ka, (const float4*)rec, n, ng,
                            (const float2*)B, (const float2*)A, out_acc);
     return hipGetLastError();
