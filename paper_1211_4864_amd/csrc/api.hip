@@ -253,11 +253,18 @@ int check_ws(const Layout& L) {
 }
 
 
+WorkBuffers work_buffers(const Layout& L) {
+    return WorkBuffers{ws_at<WorkControl>(L.work_ctl), ws_at<int>(L.cell_window),
+                       ws_at<unsigned long long>(L.col_cost), ws_at<int>(L.col_xcd)};
+}
+
 // Bins into the workspace; returns (through the pointers) where cell_start,
-// the permutation and the sorted records ended up.
+// the permutation and the sorted records ended up.  then_worklist: the caller
+// builds the work list of these cells next (worklist_impl).
 int bin_impl(const double* pos, const float* mass, int64_t n, const Geom& g,
              const Layout& L, int* cell_start, int** perm_out, float4* rec,
-             int* perm_user, int** keys_out = nullptr, int** spare_out = nullptr) {
+             int* perm_user, int** keys_out = nullptr, int** spare_out = nullptr,
+             bool then_worklist = false) {
     const int nn = (int)n;
     int* ka = ws_at<int>(L.keys_a);
     int* va = ws_at<int>(L.vals_a);
@@ -270,9 +277,11 @@ int bin_impl(const double* pos, const float* mass, int64_t n, const Geom& g,
     if (L.count_sub >= 0) {
         // keys_a: keys in input order; keys_b: order of arrival, then free;
         // vals_a: place of arrival, then the sorted keys; vals_b: permutation
+        const WorkBuffers work = work_buffers(L);
         HIP_TRY(launch_counting_sort(pos, mass, nn, g, L.count_sub, ka, va, rec_in,
                                      L.count_sub ? hist : cell_start, cell_start, tmp,
-                                     reinterpret_cast<unsigned*>(kb), rec, vb, va, g_stream));
+                                     reinterpret_cast<unsigned*>(kb), rec, vb, va,
+                                     then_worklist ? &work : nullptr, g_stream));
         std::swap(va, vb);
         std::swap(ka, vb);
         if (perm_user) {
@@ -324,11 +333,6 @@ int rcb_impl(int64_t n, const Geom& g, const Layout& L, const int* cell_start,
     return HACC_SR_OK;
 }
 
-WorkBuffers work_buffers(const Layout& L) {
-    return WorkBuffers{ws_at<WorkControl>(L.work_ctl), ws_at<int>(L.cell_window),
-                       ws_at<unsigned long long>(L.col_cost), ws_at<int>(L.col_xcd)};
-}
-
 // Work list of the RCB leaves, cost-ordered like the chaining-mesh one.
 // Reads the number of leaves back to the host (one stream synchronisation)
 // to size the launch.
@@ -362,7 +366,8 @@ int worklist_impl(const int* cell_start, int64_t n, const Geom& g, const Layout&
                   const WorkItem** items_out, const int** n_items_dev) {
     WorkItem* items = ws_at<WorkItem>(L.items);
     const WorkBuffers b = work_buffers(L);
-    HIP_TRY(launch_worklist(cell_start, (int)n, g, L.max_items, b, items, g_stream));
+    HIP_TRY(launch_worklist(cell_start, (int)n, g, L.count_sub >= 0, L.max_items, b, items,
+                            g_stream));
     *items_out = items;
     *n_items_dev = &b.ctl->n_items;
     return HACC_SR_OK;
@@ -412,7 +417,7 @@ int force_into(const double* pos, const float* mass, int64_t n, const Geom& g,
     int* cs = ws_at<int>(L.counts);
     float4* rec = ws_at<float4>(L.rec);
     int* perm = nullptr;
-    int rc = timed(2, [&] { return bin_impl(pos, mass, n, g, L, cs, &perm, rec, nullptr); });
+    int rc = timed(2, [&] { return bin_impl(pos, mass, n, g, L, cs, &perm, rec, nullptr, nullptr, nullptr, true); });
     if (rc != HACC_SR_OK) return rc;
     const WorkItem* items;
     const int* nitems;
@@ -492,7 +497,8 @@ int hacc_sr_force_noalloc(const double* pos, const float* mass, int64_t n, doubl
     int* cs = ws_at<int>(L.counts);
     float4* rec = ws_at<float4>(L.rec);
     int* perm = nullptr;
-    if ((rc = bin_impl(pos, mass, n, g, L, cs, &perm, rec, nullptr)) != HACC_SR_OK) return rc;
+    if ((rc = bin_impl(pos, mass, n, g, L, cs, &perm, rec, nullptr, nullptr, nullptr, true)) != HACC_SR_OK)
+        return rc;
     const WorkItem* items;
     const int* nitems;
     if ((rc = worklist_impl(cs, n, g, L, &items, &nitems)) != HACC_SR_OK) return rc;
@@ -652,7 +658,7 @@ int hacc_sr_force_vjp(const double* pos, const float* mass, int64_t n,
     float4* gs = ws_at<float4>(L.gsorted);
     int* perm = nullptr;
     rc = timed(2, [&] {
-        const int r = bin_impl(pos, mass, n, g, L, cs, &perm, rec, nullptr);
+        const int r = bin_impl(pos, mass, n, g, L, cs, &perm, rec, nullptr, nullptr, nullptr, true);
         if (r != HACC_SR_OK) return r;
         HIP_TRY(launch_gather_vec3(grad_acc, perm, (int)n, gs, g_stream));
         return HACC_SR_OK;
@@ -953,7 +959,7 @@ int hacc_sr_count_pairs(const double* pos, int64_t n, double box, float r_cut,
     int* cs = ws_at<int>(L.counts);
     float4* rec = ws_at<float4>(L.rec);
     int* perm = nullptr;
-    rc = bin_impl(pos, nullptr, n, g, L, cs, &perm, rec, nullptr);
+    rc = bin_impl(pos, nullptr, n, g, L, cs, &perm, rec, nullptr, nullptr, nullptr, true);
     if (rc != HACC_SR_OK) return rc;
     const WorkItem* items;
     const int* nitems;

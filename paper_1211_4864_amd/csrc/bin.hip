@@ -13,7 +13,9 @@
 // The chaining mesh is the cell list of the particle-particle part of a
 // P^3M code (Habib et al. 2012, Sec. II); cells are at least r_cut wide so
 // that all short-range partners of a particle lie in the 27 adjacent cells.
-#include "common.h"
+#include <algorithm>
+
+#include "worklist.h"
 
 namespace hsr {
 
@@ -424,19 +426,35 @@ __global__ __launch_bounds__(kBlock) void k_radix_scatter_staged(
 
 // ---------------------------------------------------------------- counting
 // Counting sort for small sets, where the radix passes are a chain of
-// launches that one or a few blocks run (21 launches; 1003 particles 55 us,
-// 65536 107 us): the particles are counted per bucket (a cell, or its
+// launches that one or a few blocks run (18 launches; 1000 particles 49 us,
+// 65536 about 100): the particles are counted per bucket (a cell, or its
 // sub-cells where cells are well filled) as their keys are formed, placed
 // in their bucket in order of arrival, and each then finds its place by
 // counting the smaller entries of its bucket: sub-cell code, then input
-// index, as the radix sort leaves them.
+// index, as the radix sort leaves them.  Where the work list follows, its
+// windows and histogram run in the same two launches, as blocks beside the
+// sort's (each launch costs 2.2 us on the host and about 2 on the GPU).
 
 // Entry of the order array: the key bits below the bucket, then the index.
 constexpr unsigned kIndexMask = (1u << kCountingIndexBits) - 1u;
 
+// The work list's share of a launch: blocks after the sort's `first` ones
+// (none where the launch has no more).
+struct BesideWork {
+    CellUnits cells;
+    WorkBuffers b;
+    int first;
+};
+
 __global__ __launch_bounds__(kBlock) void k_place(
     const int* __restrict__ keys, const int* __restrict__ arrival,
-    const int* __restrict__ start, int n, int drop, unsigned* __restrict__ order) {
+    const int* __restrict__ start, int n, int drop, unsigned* __restrict__ order,
+    BesideWork w) {
+    if ((int)blockIdx.x >= w.first) {
+        windows_block(w.cells.cs, w.cells.g, w.b.cell_window, w.b.col_cost, w.b.ctl,
+                      blockIdx.x - w.first, gridDim.x - w.first);
+        return;
+    }
     const int i = blockIdx.x * kBlock + threadIdx.x;
     if (i >= n) return;
     const int key = keys[i];
@@ -450,7 +468,13 @@ __global__ __launch_bounds__(kBlock) void k_place(
 __global__ __launch_bounds__(kBlock) void k_order_gather(
     const unsigned* __restrict__ order, const int* __restrict__ start,
     const int* __restrict__ keys, int n, int drop, const float4* __restrict__ rec_in,
-    float4* __restrict__ rec, int* __restrict__ perm, int* __restrict__ keys_out) {
+    float4* __restrict__ rec, int* __restrict__ perm, int* __restrict__ keys_out,
+    BesideWork w_list) {
+    if ((int)blockIdx.x >= w_list.first) {
+        items_hist_block(w_list.cells, w_list.b.cell_window, nullptr, w_list.cells.g.N,
+                         w_list.b.ctl, blockIdx.x - w_list.first);
+        return;
+    }
     __shared__ __align__(16) unsigned entries[kBlock / kWave][kWave];
     const int k = blockIdx.x * kBlock + threadIdx.x;
     const int lane = lane_id(), w = threadIdx.x / kWave;
@@ -511,6 +535,12 @@ __global__ __launch_bounds__(kBlock) void k_gather_vec3(
     out[k] = make_float4(v[3 * i], v[3 * i + 1], v[3 * i + 2], 0.0f);
 }
 
+__global__ __launch_bounds__(kBlock) void k_clear_two(int* p, int n, int* q, int m) {
+    const int k = blockIdx.x * kBlock + threadIdx.x;
+    if (k < n) p[k] = 0;
+    if (k < m) q[k] = 0;
+}
+
 __global__ __launch_bounds__(kBlock) void k_fill_i32(int* p, int n, int value) {
     const int k = blockIdx.x * kBlock + threadIdx.x;
     if (k < n) p[k] = value;
@@ -567,23 +597,33 @@ hipError_t launch_scan_exclusive(const int* in, int* out, int n, int* tmp,
 hipError_t launch_counting_sort(const double* pos, const float* mass, int n, Geom g,
                                 int sub, int* keys, int* arrival, float4* rec_in,
                                 int* buckets, int* cell_start, int* tmp, unsigned* order,
-                                float4* rec, int* perm, int* keys_out, hipStream_t st) {
+                                float4* rec, int* perm, int* keys_out,
+                                const WorkBuffers* work, hipStream_t st) {
+    static_assert(kBlock == kWorkBlock, "both shares of a launch have the same blocks");
+    static_assert(kOneListParticles >= kCountingParticles, "the histogram needs no XCDs");
     if (n <= 0) return hipSuccess;
     const int drop = g.sbits - sub;
-    const int nbuckets = (g.N * g.N * g.N) << sub;
-    const dim3 grid(blocks_for(n, kBlock)), block(kBlock);
-    hipError_t e = launch_fill_i32(buckets, nbuckets + 1, 0, st);
+    const int ncell = g.N * g.N * g.N;
+    const int nbuckets = ncell << sub;
+    const int nb = blocks_for(n, kBlock);
+    const int clear = work ? std::max(nbuckets + 1, kControlInts) : nbuckets + 1;
+    hipLaunchKernelGGL(k_clear_two, dim3(blocks_for(clear, kBlock)), dim3(kBlock), 0, st,
+                       buckets, nbuckets + 1,
+                       work ? reinterpret_cast<int*>(work->ctl) : nullptr,
+                       work ? kControlInts : 0);
+    hipLaunchKernelGGL(k_cell_keys, dim3(nb), dim3(kBlock), 0, st, pos, mass, n, g, keys,
+                       arrival, rec_in, buckets, drop);
+    hipError_t e = scan_exclusive(buckets, buckets, nbuckets + 1, tmp,
+                                  buckets == cell_start ? nullptr : cell_start, sub, st);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_cell_keys, grid, block, 0, st, pos, mass, n, g, keys, arrival,
-                       rec_in, buckets, drop);
-    e = scan_exclusive(buckets, buckets, nbuckets + 1, tmp,
-                       buckets == cell_start ? nullptr : cell_start, sub, st);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_place, grid, block, 0, st, (const int*)keys, (const int*)arrival,
-                       (const int*)buckets, n, drop, order);
-    hipLaunchKernelGGL(k_order_gather, grid, block, 0, st, (const unsigned*)order,
-                       (const int*)buckets, (const int*)keys, n, drop,
-                       (const float4*)rec_in, rec, perm, keys_out);
+    const BesideWork beside{CellUnits{cell_start, g}, work ? *work : WorkBuffers{}, nb};
+    hipLaunchKernelGGL(k_place, dim3(nb + (work ? window_blocks(g.N) : 0)), dim3(kBlock), 0, st,
+                       (const int*)keys, (const int*)arrival, (const int*)buckets, n, drop,
+                       order, beside);
+    hipLaunchKernelGGL(k_order_gather, dim3(nb + (work ? blocks_for(ncell, kBlock) : 0)),
+                       dim3(kBlock), 0, st, (const unsigned*)order, (const int*)buckets,
+                       (const int*)keys, n, drop, (const float4*)rec_in, rec, perm, keys_out,
+                       beside);
     return hipGetLastError();
 }
 

@@ -52,6 +52,36 @@ constexpr int kMaxSegments = 9 * (kZRun + 2);   // stencil cells of a run
 
 constexpr int kItemI = 64;     // lanes of a wave
 
+// ---- work list: buffers and constants
+
+constexpr int kCostBuckets = 128;
+constexpr int kXcds = 8;            // XCDs of an MI355X
+// Item splitting (item_limit): waves the chip holds at 8 per SIMD, and the
+// number of steps below which an item is not split, in a set that fills the
+// chip and in the smallest.
+constexpr int kResidentWaves = 8192;
+constexpr int kMinSteps = 256;
+constexpr int kFewestSteps = 16;
+// Items that splitting may add (the bound is in item_limit).
+constexpr int kMaxSplitItems = 2 * kResidentWaves;
+
+struct WorkControl {
+    unsigned long long pairs;             // pair work of all units
+    int n_items;
+    int pad;
+    int count[kXcds * kCostBuckets];      // items per (list, cost bucket)
+    int taken[kXcds * kCostBuckets];      // ranks handed out to blocks
+};
+
+constexpr int kControlInts = (int)(sizeof(WorkControl) / sizeof(int));
+
+struct WorkBuffers {
+    WorkControl* ctl;
+    int* cell_window;
+    unsigned long long* col_cost;
+    int* col_xcd;
+};
+
 // ---- launch wrappers (each defined in the translation unit of its kernels)
 
 // binning (bin.hip)
@@ -63,13 +93,18 @@ hipError_t launch_cell_keys(const double* pos, const float* mass, int n,
 // 262144 72 / 129, 32768 46 / 68, 1000 20 / 49; at 1030301 it is 185 / 160
 // (random single-entry atomics and writes).
 constexpr int kCountingParticles = 1 << 19;
-// Its entries hold the input index in their low bits.
+// Sets whose work list is a single one in decreasing cost; larger ones have
+// one per XCD.
+constexpr int kOneListParticles = kCountingParticles;
+// The sort's entries hold the input index in their low bits.
 constexpr int kCountingIndexBits = 26;
 // buckets: (cells << sub) + 1 counters, cell_start itself when sub is 0.
+// work: also form the work list's windows and histogram there (or null).
 hipError_t launch_counting_sort(const double* pos, const float* mass, int n, Geom g,
                                 int sub, int* keys, int* arrival, float4* rec_in,
                                 int* buckets, int* cell_start, int* tmp, unsigned* order,
-                                float4* rec, int* perm, int* keys_out, hipStream_t st);
+                                float4* rec, int* perm, int* keys_out,
+                                const WorkBuffers* work, hipStream_t st);
 hipError_t launch_cell_hist(const int* keys_sorted, int n, int sbits,
                             int* counts, hipStream_t st);
 size_t scan_tmp_ints(int n);
@@ -87,32 +122,10 @@ hipError_t launch_gather_vec3(const float* v, const int* perm, int n,
 hipError_t launch_fill_i32(int* p, int n, int value, hipStream_t st);
 
 // work list (worklist.hip)
-constexpr int kCostBuckets = 128;
-constexpr int kXcds = 8;            // XCDs of an MI355X
-// Item splitting (item_limit): waves the chip holds at 8 per SIMD, and the
-// number of steps below which an item is not split.
-constexpr int kResidentWaves = 8192;
-constexpr int kMinSteps = 256;
-// Items that splitting may add (the bound is in item_limit).
-constexpr int kMaxSplitItems = 2 * kResidentWaves;
-
-struct WorkControl {
-    unsigned long long pairs;             // pair work of all units
-    int n_items;
-    int pad;
-    int count[kXcds * kCostBuckets];      // items per (list, cost bucket)
-    int taken[kXcds * kCostBuckets];      // ranks handed out to blocks
-};
-
-struct WorkBuffers {
-    WorkControl* ctl;
-    int* cell_window;
-    unsigned long long* col_cost;
-    int* col_xcd;
-};
-
-hipError_t launch_worklist(const int* cell_start, int n, Geom g, int max_items,
-                           const WorkBuffers& b, WorkItem* items, hipStream_t st);
+// started: launch_counting_sort has formed the windows and the histogram.
+hipError_t launch_worklist(const int* cell_start, int n, Geom g, bool started,
+                           int max_items, const WorkBuffers& b, WorkItem* items,
+                           hipStream_t st);
 hipError_t launch_worklist_leaves(const int* cell_start, const int* leaf_start,
                                   const int* n_leaves_dev, int n_leaves,
                                   const int* keys_sorted, int n, Geom g, int max_items,

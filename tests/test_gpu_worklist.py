@@ -50,3 +50,28 @@ def test_split_items_match_oracle(cuda, n, clump, box):
           f"{np.max(dev / np.maximum(bound, 1e-300)):.2e}", flush=True)
     assert err <= 1e-5
     assert np.all(dev <= bound)
+
+
+def test_list_modes_agree(cuda):
+    """2^19 particles take the counting sort and one list of items, one more the
+    radix sort and a list per XCD: a particle of zero mass that carries the set
+    over the border leaves the others' force and VJP as they are, to the float32
+    rounding of other groupings of the sums (the parity tests' tolerances)."""
+    n = 1 << 19
+    rng = np.random.default_rng(8)
+    pos = np.concatenate([rng.random((n - 40000, 3)), 0.3 + 0.02 * rng.random((40000, 3)),
+                          [[0.9, 0.9, 0.9]]])
+    mass = np.full(n + 1, np.float32(1.0 / n))
+    mass[n] = 0.0
+    g = cotangent(n + 1, 9)
+    g[n] = 0.0
+    fit = fit_fgrid(1.0 / 80, 3.0, 1e-5 * 128.0 ** 2)
+    p, m, gt = (torch.from_numpy(a).to(cuda) for a in (pos, mass, g))
+    sr = (1.0, fit.r_cut, fit.eps, fit.coeffs)
+    out = []
+    for k in (n, n + 1):
+        pk, mk, gk = p[:k].contiguous(), m[:k].contiguous(), gt[:k].contiguous()
+        out.append((hsr.force(pk, mk, *sr)[:n].double(), hsr.force_vjp(pk, mk, *sr, gk)[:n]))
+    for a, b, tol in zip(out[0], out[1], (1e-5, 1e-4)):
+        scale = a.norm(dim=1).clamp(min=float(a.norm(dim=1).mean()) * 0.1)
+        assert float(((a - b).norm(dim=1) / scale).max()) <= tol
