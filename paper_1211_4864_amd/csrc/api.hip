@@ -273,7 +273,6 @@ int bin_impl(const double* pos, const float* mass, int64_t n, const Geom& g,
     int* hist = ws_at<int>(L.hist);
     int* tmp = ws_at<int>(L.scan_tmp);
     float4* rec_in = ws_at<float4>(L.gsorted);
-    const int ncp = (int)(L.ncell + 1);
     if (L.count_sub >= 0) {
         // keys_a: keys in input order; keys_b: order of arrival, then free;
         // vals_a: place of arrival, then the sorted keys; vals_b: permutation
@@ -293,17 +292,14 @@ int bin_impl(const double* pos, const float* mass, int64_t n, const Geom& g,
         if (spare_out) *spare_out = vb;
         return HACC_SR_OK;
     }
-    HIP_TRY(launch_cell_keys(pos, mass, nn, g, ka, va, rec_in, g_stream));
+    HIP_TRY(launch_cell_keys(pos, mass, nn, g, ka, rec_in, g_stream));
     for (int p = 0; p < L.passes; ++p) {
-        HIP_TRY(launch_radix_pass(ka, va, kb, vb, nn, L.digit_bits * p,
+        HIP_TRY(launch_radix_pass(ka, p ? va : nullptr, kb, vb, nn, L.digit_bits * p,
                                   L.digit_bits, hist, tmp, g_stream));
         std::swap(ka, kb);
         std::swap(va, vb);
     }
-    HIP_TRY(launch_fill_i32(cell_start, ncp, 0, g_stream));
-    HIP_TRY(launch_cell_hist(ka, nn, g.sbits, cell_start, g_stream));
-    HIP_TRY(launch_scan_exclusive(cell_start, cell_start, ncp, tmp, g_stream));
-    HIP_TRY(launch_gather_records(rec_in, va, nn, rec, g_stream));
+    HIP_TRY(launch_gather_records(rec_in, va, ka, nn, g, rec, cell_start, g_stream));
     if (perm_user) {
         HIP_TRY(hipMemcpyAsync(perm_user, va, sizeof(int) * (size_t)nn,
                                hipMemcpyDeviceToDevice, g_stream));

@@ -86,8 +86,7 @@ struct WorkBuffers {
 
 // binning (bin.hip)
 hipError_t launch_cell_keys(const double* pos, const float* mass, int n,
-                            Geom g, int* keys, int* vals, float4* rec,
-                            hipStream_t st);
+                            Geom g, int* keys, float4* rec, hipStream_t st);
 // Largest set of the counting sort (launch_counting_sort), which beats the
 // radix passes there: binning 512000 NFW particles takes 106 us against 139,
 // 262144 72 / 129, 32768 46 / 68, 1000 20 / 49; at 1030301 it is 185 / 160
@@ -105,21 +104,23 @@ hipError_t launch_counting_sort(const double* pos, const float* mass, int n, Geo
                                 int* buckets, int* cell_start, int* tmp, unsigned* order,
                                 float4* rec, int* perm, int* keys_out,
                                 const WorkBuffers* work, hipStream_t st);
-hipError_t launch_cell_hist(const int* keys_sorted, int n, int sbits,
-                            int* counts, hipStream_t st);
 size_t scan_tmp_ints(int n);
 hipError_t launch_scan_exclusive(const int* in, int* out, int n, int* tmp,
                                  hipStream_t st);
 int radix_blocks(int n);
 constexpr int kMaxDigitBits = 11;
+// vin null: the values are the entries' indices (first pass).
 hipError_t launch_radix_pass(const int* kin, const int* vin, int* kout,
                              int* vout, int n, int shift, int digit_bits,
                              int* hist, int* scan_tmp, hipStream_t st);
-hipError_t launch_gather_records(const float4* rec_in, const int* perm, int n,
-                                 float4* rec, hipStream_t st);
+// Also writes cell_start from the sorted keys.
+hipError_t launch_gather_records(const float4* rec_in, const int* perm, const int* keys,
+                                 int n, Geom g, float4* rec, int* cell_start,
+                                 hipStream_t st);
 hipError_t launch_gather_vec3(const float* v, const int* perm, int n,
                               float4* out, hipStream_t st);
 hipError_t launch_fill_i32(int* p, int n, int value, hipStream_t st);
+hipError_t launch_iota(int* p, int n, hipStream_t st);     // p[k] = k
 
 // work list (worklist.hip)
 // started: launch_counting_sort has formed the windows and the histogram.

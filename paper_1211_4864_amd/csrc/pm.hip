@@ -157,7 +157,6 @@ __device__ __forceinline__ void key_corner(int key, int ng, int g0[3], int t0[3]
 __global__ __launch_bounds__(kPB) void k_pm_keys(const double* __restrict__ pos,
                                                  const float* __restrict__ mass, int n, int ng,
                                                  double inv_d, int* __restrict__ keys,
-                                                 int* __restrict__ vals,
                                                  float4* __restrict__ rec) {
     const int i = blockIdx.x * kPB + threadIdx.x;
     if (i >= n) return;
@@ -165,7 +164,6 @@ __global__ __launch_bounds__(kPB) void k_pm_keys(const double* __restrict__ pos,
     double f[3];
     cic_point(pos, i, inv_d, ng, g0, f);
     keys[i] = tile_key(g0, ng);
-    vals[i] = i;
     rec[i] = make_float4((float)f[0], (float)f[1], (float)f[2], mass[i]);
 }
 
@@ -816,15 +814,19 @@ hipError_t launch_pm_accel(const double* pos, const float* mass, int n, double b
                            mass, n, ng, inv_d, mmax, mb, Q);
     } else {
         hipLaunchKernelGGL(k_pm_keys, dim3(blocks_for(n, kPB)), dim3(kPB), 0, st, pos, mass,
-                           n, ng, inv_d, ka, va, rec_in);
+                           n, ng, inv_d, ka, rec_in);
         int passes, db;
         pm_sort_shape(ng, &passes, &db);
         for (int p = 0; p < passes; ++p) {
-            const hipError_t e = launch_radix_pass(ka, va, kb, vb, n, kCellBits + db * p, db,
+            const hipError_t e = launch_radix_pass(ka, p ? va : nullptr, kb, vb, n, kCellBits + db * p, db,
                                                    hist, tmp, st);
             if (e != hipSuccess) return e;
             std::swap(ka, kb);
             std::swap(va, vb);
+        }
+        if (!passes) {                       // one tile: input order
+            const hipError_t e = launch_iota(va, n, st);
+            if (e != hipSuccess) return e;
         }
         hipLaunchKernelGGL(k_pm_gather, dim3(blocks_for(n, kPB)), dim3(kPB), 0, st,
                            (const int*)va, (const float4*)rec_in, n, rec);
