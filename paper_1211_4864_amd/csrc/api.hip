@@ -613,26 +613,27 @@ int hacc_sr_full_step(double* pos, double* vel, const float* mass, int64_t n, do
     if (!g_ws || g_ws_bytes < std::max(L.total, pm_workspace_bytes(ng, n) + 256))
         return HACC_SR_ENOSPACE;
     const int64_t m = 3 * n;
-    auto pm_kick = [&](double t) {
-        int r = timed(7, [&] {
+    auto pm_accel = [&] {
+        return timed(7, [&] {
             HIP_TRY(launch_pm_accel(pos, mass, (int)n, box, ng, sigma, n_s, ws_at<char>(0),
                                     acc_scratch, g_stream));
             return HACC_SR_OK;
         });
-        if (r != HACC_SR_OK) return r;
-        HIP_TRY(launch_kick(vel, acc_scratch, m, t, g_stream));
-        return HACC_SR_OK;
     };
-    // M_lr(t/2) (M_sr(t/n_c))^n_c M_lr(t/2)
-    if ((rc = pm_kick(0.5 * dt)) != HACC_SR_OK) return rc;
+    // M_lr(t/2) (M_sr(t/n_c))^n_c M_lr(t/2), each kick in one pass with the
+    // streams that follow it: the first half stream after the long-range kick,
+    // the last of one subcycle and the first of the next after a short-range one
+    if ((rc = pm_accel()) != HACC_SR_OK) return rc;
     const double h = dt / n_c;
+    HIP_TRY(launch_kick_stream(pos, vel, acc_scratch, m, 0.5 * dt, 0.5 * h, 1, box, g_stream));
     for (int c = 0; c < n_c; ++c) {
-        HIP_TRY(launch_stream(pos, vel, m, 0.5 * h, box, g_stream));
         if ((rc = force_into(pos, mass, n, g, P, L, acc_scratch)) != HACC_SR_OK) return rc;
-        HIP_TRY(launch_kick(vel, acc_scratch, m, h, g_stream));
-        HIP_TRY(launch_stream(pos, vel, m, 0.5 * h, box, g_stream));
+        HIP_TRY(launch_kick_stream(pos, vel, acc_scratch, m, h, 0.5 * h, c + 1 < n_c ? 2 : 1,
+                                   box, g_stream));
     }
-    return pm_kick(0.5 * dt);
+    if ((rc = pm_accel()) != HACC_SR_OK) return rc;
+    HIP_TRY(launch_kick(vel, acc_scratch, m, 0.5 * dt, g_stream));
+    return HACC_SR_OK;
 }
 
 int hacc_sr_force_vjp(const double* pos, const float* mass, int64_t n,

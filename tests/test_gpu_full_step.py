@@ -55,3 +55,34 @@ def test_full_step_matches_oracle(cuda):
     assert np.all(dv <= 3 * dt * da)
     assert np.all(dx <= 3 * dt * dt * da + 1e-15)
     assert np.all((x >= 0) & (x < box))
+
+
+@pytest.mark.parametrize("n_c", [1, 2, 4])
+def test_full_step_is_its_separate_maps(cuda, n_c):
+    """The step runs each kick in one pass with the streams around it: bitwise
+    the composition of the entry points for the separate maps (the PM and
+    short-range forces at equal positions are bitwise reproducible)."""
+    ng, n = 16, 3001
+    D = 1.0 / ng
+    rng = np.random.default_rng(74 + n_c)
+    pos = rng.random((n, 3))
+    mass = (rng.random(n) + 0.5).astype(np.float32) / n
+    r_cut, eps = float(np.float32(3.0 * D)), float(np.float32(0.164 * D * D))
+    poly = np.array([1.0, -0.5, 0.1, 0.0, 0.0, 0.0], dtype=np.float32)
+    dt = 0.05
+    m = torch.from_numpy(mass).to(cuda)
+
+    def start():
+        return (torch.from_numpy(pos.copy()).to(cuda),
+                torch.from_numpy(0.1 * np.random.default_rng(75).standard_normal((n, 3))).to(cuda))
+    x, v = start()
+    hsr.full_step(x, v, m, 1.0, ng, r_cut, eps, poly, dt, n_c)
+    y, w = start()
+    h = dt / n_c
+    hsr.kick(w, hsr.pm_accel(y, m, 1.0, ng), 0.5 * dt)
+    for _ in range(n_c):
+        hsr.stream(y, w, 0.5 * h, 1.0)
+        hsr.kick(w, hsr.force(y, m, 1.0, r_cut, eps, poly), h)
+        hsr.stream(y, w, 0.5 * h, 1.0)
+    hsr.kick(w, hsr.pm_accel(y, m, 1.0, ng), 0.5 * dt)
+    assert torch.equal(x, y) and torch.equal(v, w)
