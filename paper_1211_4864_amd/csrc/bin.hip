@@ -140,12 +140,13 @@ __device__ __forceinline__ int block_excl_scan(int v, int* total) {
     return base + incl - v;
 }
 
+template <int ITEMS>
 __global__ __launch_bounds__(kBlock) void k_scan_reduce(
     const int* __restrict__ in, int n, int* __restrict__ bsum) {
-    const int64_t base = (int64_t)blockIdx.x * kTile;
+    const int64_t base = (int64_t)blockIdx.x * (kBlock * ITEMS);
     int s = 0;
 #pragma unroll
-    for (int it = 0; it < kItems; ++it) {
+    for (int it = 0; it < ITEMS; ++it) {
         const int64_t e = base + it * kBlock + threadIdx.x;
         if (e < n) s += in[e];
     }
@@ -182,14 +183,15 @@ __global__ __launch_bounds__(kBlock) void k_scan_single(int* __restrict__ a,
 // scanned, else the sum of the blocks before it, which the block adds up
 // itself.  With `every`, the scan at each 2^every-th entry also goes to
 // `heads` (the cells' starts among those of their sub-cells).
+template <int ITEMS>
 __global__ __launch_bounds__(kBlock) void k_scan_apply(
     const int* in, int* out, int n, const int* __restrict__ bsum, bool scanned,
     int* __restrict__ heads, int every) {
-    const int64_t b = (int64_t)blockIdx.x * kTile + (int64_t)threadIdx.x * kItems;
-    int v[kItems];
+    const int64_t b = (int64_t)blockIdx.x * (kBlock * ITEMS) + (int64_t)threadIdx.x * ITEMS;
+    int v[ITEMS];
     int s = 0;
 #pragma unroll
-    for (int q = 0; q < kItems; ++q) {
+    for (int q = 0; q < ITEMS; ++q) {
         v[q] = (b + q < n) ? in[b + q] : 0;
         s += v[q];
     }
@@ -203,7 +205,7 @@ __global__ __launch_bounds__(kBlock) void k_scan_apply(
     }
     int pre = block_excl_scan(s, &tot) + carry;
 #pragma unroll
-    for (int q = 0; q < kItems; ++q) {
+    for (int q = 0; q < ITEMS; ++q) {
         if (b + q < n) {
             out[b + q] = pre;
             if (heads && ((b + q) & ((1 << every) - 1)) == 0) heads[(b + q) >> every] = pre;
@@ -576,6 +578,10 @@ __global__ __launch_bounds__(kBlock) void k_fill_i32(int* p, int n, int value) {
 
 inline int blocks_for(int64_t n, int per) { return (int)((n + per - 1) / per); }
 
+// Block sums that every block of k_scan_apply adds up itself: eight loads per
+// thread at most, less than the launch of k_scan_single.
+constexpr int kOwnCarryBlocks = 2048;
+
 }  // namespace
 
 hipError_t launch_cell_keys(const double* pos, const float* mass, int n,
@@ -586,23 +592,38 @@ hipError_t launch_cell_keys(const double* pos, const float* mass, int n,
     return hipGetLastError();
 }
 
-size_t scan_tmp_ints(int n) { return (size_t)blocks_for(n, kTile) + 1; }
+namespace {
+// Entries per thread of a scan: 16, or 4 for arrays of at most 2048 blocks of
+// those, whose launches are latency-bound (74089 entries: 19 blocks of 16 per
+// thread take 6 us each for the sums and for the scan, 73 blocks of 4 half).
+constexpr int kFewItems = 4;
+bool few_items(int n) { return blocks_for(n, kBlock * kFewItems) <= kOwnCarryBlocks; }
+}  // namespace
+
+// Room for the block sums of any array of at most n entries.
+size_t scan_tmp_ints(int n) {
+    return (size_t)std::max(blocks_for(n, kTile),
+                            std::min(blocks_for(n, kBlock * kFewItems), kOwnCarryBlocks)) + 1;
+}
 
 namespace {
-// Block sums that every block of k_scan_apply adds up itself: eight loads per
-// thread at most, less than the launch of k_scan_single.
-constexpr int kOwnCarryBlocks = 2048;
-
 hipError_t scan_exclusive(const int* in, int* out, int n, int* tmp, int* heads, int every,
                           hipStream_t st) {
     if (n <= 0) return hipSuccess;
+    const dim3 block(kBlock);
+    if (few_items(n)) {
+        const int nb = blocks_for(n, kBlock * kFewItems);
+        if (nb > 1)
+            hipLaunchKernelGGL(k_scan_reduce<kFewItems>, dim3(nb), block, 0, st, in, n, tmp);
+        hipLaunchKernelGGL(k_scan_apply<kFewItems>, dim3(nb), block, 0, st, in, out, n,
+                           (const int*)tmp, false, heads, every);
+        return hipGetLastError();
+    }
     const int nb = blocks_for(n, kTile);
     const bool scanned = nb > kOwnCarryBlocks;
-    if (nb > 1)
-        hipLaunchKernelGGL(k_scan_reduce, dim3(nb), dim3(kBlock), 0, st, in, n, tmp);
-    if (scanned)
-        hipLaunchKernelGGL(k_scan_single, dim3(1), dim3(kBlock), 0, st, tmp, nb);
-    hipLaunchKernelGGL(k_scan_apply, dim3(nb), dim3(kBlock), 0, st, in, out, n,
+    hipLaunchKernelGGL(k_scan_reduce<kItems>, dim3(nb), block, 0, st, in, n, tmp);
+    if (scanned) hipLaunchKernelGGL(k_scan_single, dim3(1), block, 0, st, tmp, nb);
+    hipLaunchKernelGGL(k_scan_apply<kItems>, dim3(nb), block, 0, st, in, out, n,
                        (const int*)tmp, scanned, heads, every);
     return hipGetLastError();
 }
