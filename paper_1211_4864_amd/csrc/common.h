@@ -34,15 +34,18 @@ struct PairParams {
     float dq3[5];
 };
 
-// One unit of pair-kernel work: T = i_count target particles of one cell,
-// processed by one wave with ksplit lanes per target (T * ksplit <= 64).
+// One unit of pair-kernel work: T = i_count target particles of one run of
+// cells, processed by one wave with ksplit lanes per target (T * ksplit <= 64).
 struct WorkItem {
-    int i_begin;      // first sorted entry of the targets
-    int i_count;      // number of targets T (1..kItemI)
-    int key;          // first cell of the item's run of cells
-    short ksplit;     // lanes per target, a power of two
-    short zlen;       // cells in the run: key, key + 1, ... along z
+    int i_begin;             // first sorted entry of the targets
+    int key;                 // first cell of the item's run of cells
+    short cx, cy;            // its column
+    unsigned char i_count;   // number of targets T (1..kItemI)
+    unsigned char ksplit;    // lanes per target, a power of two
+    unsigned char zlen;      // cells in the run: key, key + 1, ... along z
+    unsigned char pad;
 };
+static_assert(sizeof(WorkItem) == 16, "one 16-byte load");
 
 // Small cells are merged into runs of up to kZRun cells along z (one item,
 // one source window of 3 x 3 x (zlen + 2) cells) when a whole aligned block

@@ -132,15 +132,17 @@ struct Segments {
 // size for lanes past the stencil), a register copy of the table's offsets
 // for the segment searches.  Must be called by the whole wave.
 __device__ int build_segments(const WorkItem& it, const int* __restrict__ cs,
-                              const Geom& g, Segments& sg, int* segoff, int* mycnt) {
+                              const Geom& g, Segments& sg, int* segoff, int* mycnt,
+                              int* mycode) {
     const int lane = threadIdx.x;
     const int N = g.N;
-    const int cz = it.key % N, cy = (it.key / N) % N, cx = it.key / (N * N);
-    const int zw = it.zlen + 2;          // window cells along z
+    const int cx = it.cx, cy = it.cy, cz = it.key - (cx * N + cy) * N;
+    const int zw = it.zlen + 2;          // window cells along z: 3 or 4
     int cnt = 0, start = 0, code = 0;
     if (lane < 9 * zw) {
-        const int ab = lane / zw;
-        const int a = ab / 3 - 1, b = ab % 3 - 1, c = lane % zw - 1;
+        static_assert(kZRun == 2, "zw is 3 or 4");
+        const int ab = zw == 3 ? lane / 3 : lane >> 2;
+        const int a = ab / 3 - 1, b = ab % 3 - 1, c = lane - ab * zw - 1;
         int x = cx + a, y = cy + b, z = cz + c;
         bool ok = true;
         if (g.periodic) {
@@ -161,6 +163,7 @@ __device__ int build_segments(const WorkItem& it, const int* __restrict__ cs,
     const int total = __shfl(incl, kWave - 1);
     *segoff = incl - cnt;
     *mycnt = cnt;
+    *mycode = code;
     if (lane < kSeg) {
         sg.off[lane] = incl - cnt;
         sg.start[lane] = start;
@@ -178,15 +181,13 @@ __device__ int build_segments(const WorkItem& it, const int* __restrict__ cs,
 // per-source cull: the kept sources and their order do not change (the
 // rounds that stage them do, and with them the grouping of the float32
 // partial sums).  Must be called by the whole wave, with each lane's count
-// from build_segments.
-__device__ int cull_segments(const WorkItem& it, Segments& sg, int cnt, float4 lo,
+// and code from build_segments.
+__device__ int cull_segments(const WorkItem& it, Segments& sg, int cnt, int code, float4 lo,
                              float4 hi, float cull2, float Lc, int* segoff) {
     const int lane = threadIdx.x;
-    const int zw = it.zlen + 2;
-    if (lane < 9 * zw && cnt > 0) {
-        const int ab = lane / zw;
-        const float a = (float)(ab / 3 - 1), b = (float)(ab % 3 - 1);
-        const float c = (float)(lane % zw - 1) - 0.5f * (float)it.zlen;
+    if (cnt > 0) {
+        const float a = (float)(code & 255) - 1.0f, b = (float)((code >> 8) & 255) - 1.0f;
+        const float c = ((float)((code >> 16) & 255) - 1.0f) - 0.5f * (float)it.zlen;
         const float pad = 1e-5f * Lc;
         const float xl = (a - 0.5f) * Lc - pad, xh = (a + 0.5f) * Lc + pad;
         const float yl = (b - 0.5f) * Lc - pad, yh = (b + 0.5f) * Lc + pad;
@@ -336,14 +337,14 @@ __device__ __forceinline__ int compact_round(const Round<WithG, TILE>& R, float4
     return fill;
 }
 
-// Bounding box of the item's targets (lanes without a target hold none).
-__device__ __forceinline__ void target_box(float4 x, bool valid, float4* lo,
+// Bounding box of the item's targets (lanes without a target hold none; the ks
+// lanes of a target hold the same).
+__device__ __forceinline__ void target_box(float4 x, bool valid, int ks, float4* lo,
                                            float4* hi) {
     const float inf = __builtin_huge_valf();
     float a = valid ? x.x : inf, b = valid ? x.y : inf, c = valid ? x.z : inf;
     float d = valid ? x.x : -inf, e = valid ? x.y : -inf, f = valid ? x.z : -inf;
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) {
+    for (int o = ks; o < kWave; o <<= 1) {
         a = fminf(a, __shfl_xor(a, o));
         b = fminf(b, __shfl_xor(b, o));
         c = fminf(c, __shfl_xor(c, o));
@@ -470,8 +471,8 @@ __global__ __launch_bounds__(kWave, kMinWaves) void k_pair_force(
     const WorkItem it = items[blockIdx.x];
     const int lane = threadIdx.x;
     const float Lc = g.Lc_f;
-    int segoff, mycnt;
-    build_segments(it, cs, g, sg, &segoff, &mycnt);
+    int segoff, mycnt, mycode;
+    build_segments(it, cs, g, sg, &segoff, &mycnt, &mycode);
     const Lanes L = lane_map(it);
     // output slot, loaded now so that its latency overlaps the rounds
     const int dst = perm[L.ki >= 0 ? L.ki : it.i_begin];
@@ -479,8 +480,8 @@ __global__ __launch_bounds__(kWave, kMinWaves) void k_pair_force(
     __syncthreads();
     xi = target_in_frame(xi, L.ki, it, sg, Lc);
     float4 lo, hi;
-    target_box(xi, L.ki >= 0, &lo, &hi);
-    const int total = cull_segments(it, sg, mycnt, lo, hi, P.cull2, Lc, &segoff);
+    target_box(xi, L.ki >= 0, L.ks, &lo, &hi);
+    const int total = cull_segments(it, sg, mycnt, mycode, lo, hi, P.cull2, Lc, &segoff);
     const float mref = uniform(__shfl(xi.w, 0));
     const bool targets_equal = __ballot(L.ki >= 0 && xi.w != mref) == 0ull;
     const float4 pad = pad_source(lo, Lc);
@@ -537,14 +538,14 @@ __global__ __launch_bounds__(kWave) void k_pair_count(
     if ((int)blockIdx.x >= *n_items_dev) return;
     const WorkItem it = items[blockIdx.x];
     const float Lc = g.Lc_f;
-    int segoff, mycnt;
-    const int total = build_segments(it, cs, g, sg, &segoff, &mycnt);
+    int segoff, mycnt, mycode;
+    const int total = build_segments(it, cs, g, sg, &segoff, &mycnt, &mycode);
     const Lanes L = lane_map(it);
     float4 xi = L.ki >= 0 ? rec[L.ki] : make_float4(0.f, 0.f, 0.f, 0.f);
     __syncthreads();
     xi = target_in_frame(xi, L.ki, it, sg, Lc);
     float4 lo, hi;
-    target_box(xi, L.ki >= 0, &lo, &hi);
+    target_box(xi, L.ki >= 0, L.ks, &lo, &hi);
     __syncthreads();
     unsigned long long inside = 0;
     int kept = 0;
@@ -696,8 +697,8 @@ __global__ __launch_bounds__(kWave, kVMinWaves) void k_pair_vjp(
     const WorkItem it = items[blockIdx.x];
     const int lane = threadIdx.x;
     const float Lc = g.Lc_f;
-    int segoff, mycnt;
-    build_segments(it, cs, g, sg, &segoff, &mycnt);
+    int segoff, mycnt, mycode;
+    build_segments(it, cs, g, sg, &segoff, &mycnt, &mycode);
     const Lanes L = lane_map(it);
     // output slot, loaded now so that its latency overlaps the rounds
     const int dst = perm[L.ki >= 0 ? L.ki : it.i_begin];
@@ -706,8 +707,8 @@ __global__ __launch_bounds__(kWave, kVMinWaves) void k_pair_vjp(
     __syncthreads();
     xk = target_in_frame(xk, L.ki, it, sg, Lc);
     float4 lo, hi;
-    target_box(xk, L.ki >= 0, &lo, &hi);
-    const int total = cull_segments(it, sg, mycnt, lo, hi, P.cull2, Lc, &segoff);
+    target_box(xk, L.ki >= 0, L.ks, &lo, &hi);
+    const int total = cull_segments(it, sg, mycnt, mycode, lo, hi, P.cull2, Lc, &segoff);
     const float mref = uniform(__shfl(xk.w, 0));
     const bool targets_equal = __ballot(L.ki >= 0 && xk.w != mref) == 0ull;
     const float4 pad = pad_source(lo, Lc);

@@ -218,10 +218,13 @@ __global__ __launch_bounds__(kBlock) void k_items_write(
                                        : lists * shortest + tail[rk.x] + (rr - shortest);
         WorkItem it;
         it.i_begin = u.begin + o;
-        it.i_count = targets;
         it.key = u.key;
-        it.ksplit = (short)lanes_per_target(targets);
-        it.zlen = (short)u.zlen;
+        it.cx = (short)(u.key / N / N);
+        it.cy = (short)(u.key / N % N);
+        it.i_count = (unsigned char)targets;
+        it.ksplit = (unsigned char)lanes_per_target(targets);
+        it.zlen = (unsigned char)u.zlen;
+        it.pad = 0;
         if (slot < max_items) out[slot] = it;
     }
 }
