@@ -51,7 +51,7 @@ WORKLOADS = {
 
 
 TRAFFIC_PROFILE = os.path.join(ROOT, "profiles", "pair_kernels_cfg3_counters.md")
-KERNEL_SOURCES = ("pair.hip", "common.h", "worklist.hip")
+KERNEL_SOURCES = ("pair.hip", "common.h", "worklist.h", "worklist.hip")
 
 
 def kernel_source_hash() -> str:

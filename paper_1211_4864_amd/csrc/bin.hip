@@ -1,12 +1,11 @@
-// Chaining-mesh binning: cell keys and cell-relative float32 records, then
-// for small sets a counting sort over the cells (its own section below), for
-// larger ones
-// stable LSD radix passes (each block orders its tile of keys in LDS and
-// writes each digit's keys out as one run), and the gather of the records into
-// sorted order, which also writes cell_start.  The sort key is the cell index followed by the Morton code
-// of the particle's sub-cell (4^3 per cell when the key has room), so a
-// cell's particles are grouped spatially and, within a sub-cell, keep their
-// input order: the binning is deterministic.
+// Chaining-mesh binning: cell keys and cell-relative float32 records, then for
+// small sets a counting sort over the cells (its own section below), for larger
+// ones stable LSD radix passes (each block orders its tile of keys in LDS and
+// writes each digit's keys out as one run) and the gather of the records into
+// sorted order, which also writes cell_start.  The sort key is the cell index
+// followed by the Morton code of the particle's sub-cell (4^3 per cell when the
+// key has room), so a cell's particles are grouped spatially and, within a
+// sub-cell, keep their input order: the binning is deterministic.
 //
 // The chaining mesh is the cell list of the particle-particle part of a
 // P^3M code (Habib et al. 2012, Sec. II); cells are at least r_cut wide so
