@@ -24,9 +24,9 @@
 //  - Larger sets are sorted by tiles of 8^3 cells first: one pass writes each
 //    particle's lower-corner cell (tile, then cell in the tile) and a record
 //    (the three CIC fractions and the mass, float32), a stable LSD radix sort
-//    orders the tiles, and the records are gathered into that order.  A block
-//    takes kChunk consecutive particles and sums the deposit of each of their
-//    tiles in LDS, so that only its 9^3 sums are added to the grid.
+//    orders the tiles.  A block takes kChunk consecutive particles, gathers
+//    their records into that order and sums the deposit of each of their tiles
+//    in LDS, so that only its 9^3 sums are added to the grid.
 //  - FFT: one kernel per axis.  A workgroup transforms L lines of ng points
 //    as ng = R1 x R2 (the four-step method): each thread does a length-R1
 //    DFT in registers, multiplies by the twiddles of the length-ng transform
@@ -167,14 +167,6 @@ __global__ __launch_bounds__(kPB) void k_pm_keys(const double* __restrict__ pos,
     rec[i] = make_float4((float)f[0], (float)f[1], (float)f[2], mass[i]);
 }
 
-__global__ __launch_bounds__(kPB) void k_pm_gather(const int* __restrict__ perm,
-                                                   const float4* __restrict__ rec_in, int n,
-                                                   float4* __restrict__ rec) {
-    const int k = blockIdx.x * kPB + threadIdx.x;
-    if (k >= n) return;
-    rec[k] = rec_in[perm[k]];
-}
-
 // ---- deposit
 
 __device__ __forceinline__ int64_t corner_index(const int g0[3], int c, int ng) {
@@ -258,7 +250,7 @@ __global__ __launch_bounds__(kDB) void k_pm_deposit_direct(
 // Particles of a block of the sorted passes, and the fewest of one tile that
 // the block takes through LDS: below that, clearing and adding (or reading)
 // the tile's 9^3 values costs more than the particles' own 8 corners.
-constexpr int kChunk = 2048;
+constexpr int kChunk = 1024;
 constexpr int kFewest = 64;
 constexpr int kEdge = kSide + 1;
 constexpr int kCorners = kEdge * kEdge * kEdge;
@@ -336,21 +328,42 @@ __device__ __forceinline__ int64_t tile_corner_index(const int t0[3], int v, int
     return ((int64_t)x * ng + y) * ng + z;
 }
 
-// Bound by the LDS atomics (8 of 64 bits per particle); 16.8M NFW particles
-// on 256^3: 0.78 ms with the sums of equal cells formed in registers and every
-// corner added in memory, 0.27 now.
+// Gathers the block's records into tile order, for itself and for the
+// interpolation, and deposits them.  The gather waits on random 16-byte reads
+// and the deposit on LDS atomics (8 of 64 bits per particle), so that the two
+// overlap between the blocks of a CU; kChunk is small for that.  The whole solve of
+// 16.8M NFW particles on 256^3: 2.01 ms with the gather in a launch of its own
+// (0.37 ms, and 0.28 for the deposit), 1.89 now; 262144 particles on 64^3 112 ->
+// 101 us (111 with 2048 particles per block).  With every corner added in memory
+// the deposit alone takes 0.78 ms.
 __global__ __launch_bounds__(kPB) void k_pm_deposit(
-    const int* __restrict__ keys, const float4* __restrict__ rec, int n, int ng,
+    const int* __restrict__ keys, const int* __restrict__ vals,
+    const float4* __restrict__ rec_in, float4* rec, int n, int ng,
     unsigned* __restrict__ mass_max, int mass_blocks,
     unsigned long long* __restrict__ grid) {
     __shared__ Ranges r;
     __shared__ unsigned long long acc[kCorners];
+    const int first = blockIdx.x * kChunk;
+    const int m = min(kChunk, n - first);
+    {
+        constexpr int kPer = kChunk / kPB;
+        int from[kPer];
+        float4 p[kPer];
+#pragma unroll
+        for (int j = 0; j < kPer; ++j)
+            from[j] = vals[first + min((int)threadIdx.x + j * kPB, m - 1)];
+#pragma unroll
+        for (int j = 0; j < kPer; ++j) p[j] = rec_in[from[j]];
+#pragma unroll
+        for (int j = 0; j < kPer; ++j) {
+            const int q = threadIdx.x + j * kPB;
+            if (q < m) rec[first + q] = p[j];
+        }
+    }
     const double mmax = largest_mass<kPB>(mass_max, mass_blocks);
     if (!(mmax > 0.0)) return;                       // uniform: nothing to deposit
     const double scale = kFixedScale / ((double)n * mmax);
-    const int first = blockIdx.x * kChunk;
-    const int m = min(kChunk, n - first);
-    find_ranges(keys, first, m, r);
+    find_ranges(keys, first, m, r);                  // also: the block's records are written
     for (int q = threadIdx.x; q < m; q += kPB) {
         if (r.tile[q] >= 0) continue;
         const float4 p = rec[first + q];
@@ -743,8 +756,8 @@ void pm_sort_shape(int ng, int* passes, int* digit_bits) {
 // Whether to deposit and interpolate in input order, without the sort: its
 // launches cost more than the scattered accesses to a grid (microseconds,
 // direct / sorted, NFW): 32^3 with 32768 particles 42 / 76, with 262144
-// 135 / 89; 64^3 50000 60 / 101, 262144 163 / 111; 128^3 16384 91 / 171,
-// 262144 238 / 215; 256^3 262144 530 / 555, 2097152 1427 / 949.
+// 135 / 73; 64^3 50000 60 / 101, 262144 163 / 101; 128^3 16384 91 / 171,
+// 262144 238 / 186; 256^3 262144 530 / 555, 2097152 1427 / 937.
 bool direct_pm(int ng, int64_t n) {
     return n <= (1 << 17) + std::min<int64_t>((int64_t)ng * ng * ng / 64, 1 << 18);
 }
@@ -834,10 +847,9 @@ hipError_t launch_pm_accel(const double* pos, const float* mass, int n, double b
             const hipError_t e = launch_iota(va, n, st);
             if (e != hipSuccess) return e;
         }
-        hipLaunchKernelGGL(k_pm_gather, dim3(blocks_for(n, kPB)), dim3(kPB), 0, st,
-                           (const int*)va, (const float4*)rec_in, n, rec);
         hipLaunchKernelGGL(k_pm_deposit, dim3(blocks_for(n, kChunk)), dim3(kPB), 0, st,
-                           (const int*)ka, (const float4*)rec, n, ng, mmax, mb, Q);
+                           (const int*)ka, (const int*)va, (const float4*)rec_in, rec, n, ng,
+                           mmax, mb, Q);
     }
     FftArgs fa{};
     fa.a = A;
