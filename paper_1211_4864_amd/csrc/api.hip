@@ -279,7 +279,8 @@ int bin_impl(const double* pos, const float* mass, int64_t n, const Geom& g,
         const WorkBuffers work = work_buffers(L);
         HIP_TRY(launch_counting_sort(pos, mass, nn, g, L.count_sub, ka, va, rec_in,
                                      L.count_sub ? hist : cell_start, cell_start, tmp,
-                                     reinterpret_cast<unsigned*>(kb), rec, vb, va,
+                                     reinterpret_cast<unsigned*>(kb), &work.ctl->any_heavy,
+                                     rec, vb, va,
                                      then_worklist ? &work : nullptr, g_stream));
         std::swap(va, vb);
         std::swap(ka, vb);

@@ -68,42 +68,90 @@ __device__ __forceinline__ int axis_sub(double xw, int c, const Geom& g, int S) 
     return (int)t;
 }
 
+// How k_cell_keys counts the particles of each bucket key >> drop (counting
+// sort only), leaving in vals[i] the particle's place among those of its bucket
+// in order of arrival.
+enum { kNoCounts = 0, kCountEach = 1, kCountBlock = 2 };
+
+// Slots of a block's table of buckets, four per particle.
+constexpr int kCountTableBits = 10;
+constexpr int kCountTable = 1 << kCountTableBits;
+
 // Sort key (cell index, then the sub-cell Morton code) and the float32
 // record (position relative to the cell's lower corner, mass) of every
 // particle, in input order.
-// counts (counting sort only): vals[i] is the particle's place, in order
-// of arrival, among those of its bucket key >> drop.
+// kCountEach adds every particle to its bucket's counter.  Adds on one address
+// take 25 ns each in turn, so that a concentrated set is bound by them:
+// kCountBlock first counts a block's particles per bucket in an LDS table (open
+// addressing; it always has a free slot) and adds once per bucket and block,
+// 2048 times at most instead of 524288 (all on one point: 13 ms of adds; the
+// whole sort takes 0.09 now).  Also clears zero[i] where zero is given.
+template <int COUNTS>
 __global__ __launch_bounds__(kBlock) void k_cell_keys(
     const double* __restrict__ pos, const float* __restrict__ mass, int n,
     Geom g, int* __restrict__ keys, int* __restrict__ vals,
-    float4* __restrict__ rec, int* __restrict__ counts, int drop) {
+    float4* __restrict__ rec, int* __restrict__ counts, int drop,
+    unsigned* __restrict__ zero) {
+    constexpr bool kTable = COUNTS == kCountBlock;
+    __shared__ int owner[kTable ? kCountTable : 1];   // bucket of a slot, -1: free
+    __shared__ int held[kTable ? kCountTable : 1];    // its particles
+    __shared__ int base[kTable ? kCountTable : 1];    // and the place of the first
     const int i = blockIdx.x * kBlock + threadIdx.x;
-    if (i >= n) return;
-    double xw, yw, zw;
-    const int cx = axis_cell(pos[3 * (int64_t)i], g, &xw);
-    const int cy = axis_cell(pos[3 * (int64_t)i + 1], g, &yw);
-    const int cz = axis_cell(pos[3 * (int64_t)i + 2], g, &zw);
-    const int key = (cx * g.N + cy) * g.N + cz;
-    int code = 0;
-    const int levels = g.sbits / 3;
-    if (levels > 0) {
-        const int S = 1 << levels;
-        const int sx = axis_sub(xw, cx, g, S);
-        const int sy = axis_sub(yw, cy, g, S);
-        const int sz = axis_sub(zw, cz, g, S);
-        for (int b = 0; b < levels; ++b)
-            code |= (((sx >> b) & 1) << (3 * b + 2)) |
-                    (((sy >> b) & 1) << (3 * b + 1)) | (((sz >> b) & 1) << (3 * b));
+    if (kTable) {
+        for (int v = threadIdx.x; v < kCountTable; v += kBlock) {
+            owner[v] = -1;
+            held[v] = 0;
+        }
+    } else if (i >= n) {
+        return;
     }
-    const int full = (key << g.sbits) | code;
-    keys[i] = full;
-    if (counts) vals[i] = atomicAdd(&counts[full >> drop], 1);
-    float4 r;
-    r.x = (float)(xw - (double)cx * g.Lc);
-    r.y = (float)(yw - (double)cy * g.Lc);
-    r.z = (float)(zw - (double)cz * g.Lc);
-    r.w = mass ? mass[i] : 0.0f;
-    rec[i] = r;
+    int full = 0;
+    if (i < n) {
+        double xw, yw, zw;
+        const int cx = axis_cell(pos[3 * (int64_t)i], g, &xw);
+        const int cy = axis_cell(pos[3 * (int64_t)i + 1], g, &yw);
+        const int cz = axis_cell(pos[3 * (int64_t)i + 2], g, &zw);
+        const int key = (cx * g.N + cy) * g.N + cz;
+        int code = 0;
+        const int levels = g.sbits / 3;
+        if (levels > 0) {
+            const int S = 1 << levels;
+            const int sx = axis_sub(xw, cx, g, S);
+            const int sy = axis_sub(yw, cy, g, S);
+            const int sz = axis_sub(zw, cz, g, S);
+            for (int b = 0; b < levels; ++b)
+                code |= (((sx >> b) & 1) << (3 * b + 2)) |
+                        (((sy >> b) & 1) << (3 * b + 1)) | (((sz >> b) & 1) << (3 * b));
+        }
+        full = (key << g.sbits) | code;
+        keys[i] = full;
+        if (COUNTS == kCountEach) vals[i] = atomicAdd(&counts[full >> drop], 1);
+        if (zero) zero[i] = 0u;
+        float4 r;
+        r.x = (float)(xw - (double)cx * g.Lc);
+        r.y = (float)(yw - (double)cy * g.Lc);
+        r.z = (float)(zw - (double)cz * g.Lc);
+        r.w = mass ? mass[i] : 0.0f;
+        rec[i] = r;
+    }
+    if (!kTable) return;
+    __syncthreads();
+    const int bucket = full >> drop;
+    int v = 0, place = -1;
+    if (i < n) {
+        // at most kBlock of the kCountTable slots are taken: the search ends
+        v = (int)(((unsigned)bucket * 2654435761u) >> (32 - kCountTableBits));
+        for (;;) {
+            const int had = atomicCAS(&owner[v], -1, bucket);
+            if (had == -1 || had == bucket) break;
+            v = (v + 1) & (kCountTable - 1);
+        }
+        place = atomicAdd(&held[v], 1);
+    }
+    __syncthreads();
+    if (place == 0) base[v] = atomicAdd(&counts[bucket], held[v]);
+    __syncthreads();
+    if (i < n) vals[i] = base[v] + place;
 }
 
 // ---------------------------------------------------------------- scan
@@ -181,11 +229,12 @@ __global__ __launch_bounds__(kBlock) void k_scan_single(int* __restrict__ a,
 // Scan of one tile plus its carry: bsum[block] when the block sums have been
 // scanned, else the sum of the blocks before it, which the block adds up
 // itself.  With `every`, the scan at each 2^every-th entry also goes to
-// `heads` (the cells' starts among those of their sub-cells).
+// `heads` (the cells' starts among those of their sub-cells).  With `large`,
+// it is set to 1 if an entry is at least `least`.
 template <int ITEMS>
 __global__ __launch_bounds__(kBlock) void k_scan_apply(
     const int* in, int* out, int n, const int* __restrict__ bsum, bool scanned,
-    int* __restrict__ heads, int every) {
+    int* __restrict__ heads, int every, int* __restrict__ large, int least) {
     const int64_t b = (int64_t)blockIdx.x * (kBlock * ITEMS) + (int64_t)threadIdx.x * ITEMS;
     int v[ITEMS];
     int s = 0;
@@ -193,6 +242,12 @@ __global__ __launch_bounds__(kBlock) void k_scan_apply(
     for (int q = 0; q < ITEMS; ++q) {
         v[q] = (b + q < n) ? in[b + q] : 0;
         s += v[q];
+    }
+    if (large) {
+        bool any = false;
+#pragma unroll
+        for (int q = 0; q < ITEMS; ++q) any = any || v[q] >= least;
+        if (any) *large = 1;
     }
     int tot, carry = 0;
     if (scanned) {
@@ -430,9 +485,57 @@ __global__ __launch_bounds__(kBlock) void k_radix_scatter_staged(
 // index, as the radix sort leaves them.  Where the work list follows, its
 // windows and histogram run in the same two launches, as blocks beside the
 // sort's (each launch costs 2.2 us on the host and about 2 on the GPU).
+//
+// Heavy buckets (heavy_least) do not count entry against entry, which is
+// quadratic: the particles of one block of k_place are counted per sort key, and
+// those counts added up per segment of the input, so that a particle's place
+// is the keys below its own, its key's counts in the segments before, and the
+// equal keys before it in its own segment.  All of it linear in n: with 524288
+// particles on one point the sort takes 92 us (22.5 ms counted one by one, 190
+// by radix passes), with 65536 38 (1704, 94), with a tenth of 524288 there 112
+// (1567, 118); 524288 in a few cells of 100^3, where a bucket is 64 keys,
+// 300 (3165, 170).
 
 // Entry of the order array: the key bits below the bucket, then the index.
 constexpr unsigned kIndexMask = (1u << kCountingIndexBits) - 1u;
+
+// A bucket is heavy from heavy_least entries on.  Its entries of the order
+// array then hold its counts, cleared by k_cell_keys: one word per sort key (all
+// of its particles; unused where the bucket is one key), then per sort key a
+// row of 16-bit counts, one per segment of 2^heavy_seg_bits particles of the
+// input: the shortest segments, from one block of 256 particles to 16 blocks,
+// whose counts fit into the bucket's entries.  A block of a longer segment
+// searches the keys of those before it.
+// Where it lies: counting one by one takes 1 us per 64 entries of the bucket in
+// each of its waves, in turn; counting per segment 11 us, and 2.5 more per
+// block that is searched, which buckets of 64 keys need sooner.
+constexpr int kHeavyLeast = 1024, kHeavyLeast64 = 2048;
+constexpr int kLongestSegBits = 12;      // a segment's count fits 16 bits
+
+// Words of a sort key's row, and of all the counts.
+__host__ __device__ constexpr int heavy_row(int n, int seg_bits) {
+    return (((n - 1) >> seg_bits) + 2) / 2;
+}
+__host__ __device__ constexpr int heavy_words(int n, int drop, int seg_bits) {
+    return (1 << drop) * (1 + heavy_row(n, seg_bits));
+}
+
+// For a bucket of `count` >= heavy_least entries (the search ends at kLongestSegBits).
+__device__ __forceinline__ int heavy_seg_bits(int n, int drop, int count) {
+    int bits = 8;
+    while (bits < kLongestSegBits && heavy_words(n, drop, bits) > count) ++bits;
+    return bits;
+}
+
+int heavy_least(int n, int drop) {
+    return std::max(drop > 3 ? kHeavyLeast64 : kHeavyLeast,
+                    heavy_words(n, drop, kLongestSegBits));
+}
+
+// Sets that are no larger have no heavy bucket and no more than that many adds
+// on one counter, which cost as much as the tables of kCountBlock.
+constexpr int kCountEachParticles = 1023;
+static_assert(kCountEachParticles < kHeavyLeast, "small sets have no heavy bucket");
 
 // The work list's share of a launch: blocks after the sort's `first` ones
 // (none where the launch has no more).
@@ -442,20 +545,123 @@ struct BesideWork {
     int first;
 };
 
+// Equal sort keys among the block's kBlock keys in `sk`: all of them, those of
+// lower index, and the first one's index.
+struct Equal {
+    int all, before, first;
+};
+
+__device__ __forceinline__ Equal equal_keys(const int* sk, int key) {
+    Equal q{0, 0, kBlock};
+    for (int j = 0; j < kBlock; ++j) {
+        const bool same = sk[j] == key;
+        q.all += same;
+        q.before += same && j < (int)threadIdx.x;
+        if (same && q.first == kBlock) q.first = j;
+    }
+    return q;
+}
+
 __global__ __launch_bounds__(kBlock) void k_place(
     const int* __restrict__ keys, const int* __restrict__ arrival,
-    const int* __restrict__ start, int n, int drop, unsigned* __restrict__ order,
-    BesideWork w) {
+    const int* __restrict__ start, int n, int drop, int heavy,
+    unsigned* __restrict__ order, const int* __restrict__ any_heavy, BesideWork w) {
     if ((int)blockIdx.x >= w.first) {
         windows_block(w.cells.cs, w.cells.g, w.b.cell_window, w.b.col_cost, w.b.ctl,
                       blockIdx.x - w.first, gridDim.x - w.first);
         return;
     }
     const int i = blockIdx.x * kBlock + threadIdx.x;
-    if (i >= n) return;
-    const int key = keys[i];
+    const bool live = i < n;
+    const int key = live ? keys[i] : -1;
+    const int b = live ? start[key >> drop] : 0;
     const unsigned low = (unsigned)key & ((1u << drop) - 1u);
-    order[start[key >> drop] + arrival[i]] = (low << kCountingIndexBits) | (unsigned)i;
+    const bool any = n >= heavy && *any_heavy;        // uniform
+    const int count = any && live ? start[(key >> drop) + 1] - b : 0;
+    const bool is_heavy = any && count >= heavy;
+    if (live && !is_heavy) order[b + arrival[i]] = (low << kCountingIndexBits) | (unsigned)i;
+    if (!any || !__syncthreads_or(is_heavy)) return;
+    __shared__ int sk[kBlock];
+    sk[threadIdx.x] = key;
+    __syncthreads();
+    if (!is_heavy) return;
+    const Equal q = equal_keys(sk, key);
+    if (q.before) return;
+    const int bits = heavy_seg_bits(n, drop, count);
+    const int seg = i >> bits;
+    if (drop) atomicAdd(&order[b + low], (unsigned)q.all);
+    atomicAdd(&order[b + (1 << drop) + (int)low * heavy_row(n, bits) + (seg >> 1)],
+              (unsigned)q.all << (16 * (seg & 1)));
+}
+
+// The block's particles of heavy buckets, by input index.
+__device__ __forceinline__ void gather_heavy(
+    const unsigned* __restrict__ order, const int* __restrict__ start,
+    const int* __restrict__ keys, int n, int drop, int heavy,
+    const float4* __restrict__ rec_in, float4* __restrict__ rec, int* __restrict__ perm,
+    int* __restrict__ keys_out) {
+    __shared__ int sk[kBlock];
+    __shared__ int base[kBlock];        // by the first particle of a key
+    __shared__ int longest;             // bits of the block's longest segment
+    const int i0 = blockIdx.x * kBlock, i = i0 + (int)threadIdx.x;
+    const bool live = i < n;
+    const int key = live ? keys[i] : -1;
+    const int b = live ? start[key >> drop] : 0;
+    const int count = live ? start[(key >> drop) + 1] - b : 0;
+    const bool is_heavy = count >= heavy;
+    if (threadIdx.x == 0) longest = 0;
+    sk[threadIdx.x] = key;
+    if (!__syncthreads_or(is_heavy)) return;
+    Equal q{0, 0, kBlock};
+    int bits = 0;
+    if (is_heavy) {
+        q = equal_keys(sk, key);
+        bits = heavy_seg_bits(n, drop, count);
+        atomicMax(&longest, bits);
+    }
+    // the counts before each key's first particle, added up by 16 lanes
+    constexpr int kGroup = 16;
+    const int low = key & ((1 << drop) - 1);
+    const int seg = i >> bits;
+    const int lane = lane_id(), wave0 = (int)threadIdx.x - lane;
+    for (uint64_t left = __ballot(is_heavy && q.before == 0); left;) {
+        uint64_t mine = left;                       // the group's: first to fourth left
+#pragma unroll
+        for (int t = 0; t < kWave / kGroup; ++t) {
+            if (t < lane / kGroup) mine &= mine - 1;
+            left &= left - 1;
+        }
+        const int l = mine ? __ffsll((unsigned long long)mine) - 1 : 0;
+        const unsigned* area = order + __shfl(b, l);
+        const int lw = __shfl(low, l), sg = __shfl(seg, l);
+        const unsigned* row = area + (1 << drop) + lw * heavy_row(n, __shfl(bits, l));
+        unsigned sum = 0u;
+        if (mine) {
+            for (int v = lane % kGroup; v < lw; v += kGroup) sum += area[v];
+#pragma unroll 8
+            for (int w = lane % kGroup; w <= sg >> 1; w += kGroup) {
+                const unsigned two = row[w];
+                sum += (2 * w < sg ? two & 0xffffu : 0u) + (2 * w + 1 < sg ? two >> 16 : 0u);
+            }
+        }
+#pragma unroll
+        for (int o = 1; o < kGroup; o <<= 1) sum += (unsigned)__shfl_xor((int)sum, o);
+        if (mine && lane % kGroup == 0) base[wave0 + l] = (int)sum;
+    }
+    __syncthreads();
+    // the equal keys in the blocks before this one in its segment
+    for (int s0 = i0 >> longest << longest; s0 < i0; s0 += kBlock) {
+        __syncthreads();
+        sk[threadIdx.x] = keys[s0 + (int)threadIdx.x];
+        __syncthreads();
+        if (is_heavy && s0 >= seg << bits)
+            for (int j = 0; j < kBlock; ++j) q.before += sk[j] == key;
+    }
+    if (!is_heavy) return;
+    const int at = b + base[q.first] + q.before;
+    rec[at] = rec_in[i];
+    perm[at] = i;
+    keys_out[at] = key;
 }
 
 // A wave takes 64 consecutive entries.  Their buckets' entries are read 64 at
@@ -463,7 +669,8 @@ __global__ __launch_bounds__(kBlock) void k_place(
 // two instructions per entry where the wave lies in one bucket.
 __global__ __launch_bounds__(kBlock) void k_order_gather(
     const unsigned* __restrict__ order, const int* __restrict__ start,
-    const int* __restrict__ keys, int n, int drop, const float4* __restrict__ rec_in,
+    const int* __restrict__ keys, int n, int drop, int heavy,
+    const int* __restrict__ any_heavy, const float4* __restrict__ rec_in,
     float4* __restrict__ rec, int* __restrict__ perm, int* __restrict__ keys_out,
     BesideWork w_list) {
     if ((int)blockIdx.x >= w_list.first) {
@@ -471,18 +678,24 @@ __global__ __launch_bounds__(kBlock) void k_order_gather(
                          w_list.b.ctl, blockIdx.x - w_list.first);
         return;
     }
+    if (n >= heavy && *any_heavy)              // uniform
+        gather_heavy(order, start, keys, n, drop, heavy, rec_in, rec, perm, keys_out);
     __shared__ __align__(16) unsigned entries[kBlock / kWave][kWave];
     const int k = blockIdx.x * kBlock + threadIdx.x;
     const int lane = lane_id(), w = threadIdx.x / kWave;
-    const int k0 = k - lane;                     // the wave's first entry
-    if (k0 >= n) return;
-    const bool live = k < n;
-    const unsigned mine = live ? order[k] : 0u;
-    const int i = (int)(mine & kIndexMask);
+    if (k - lane >= n) return;
+    const unsigned mine = k < n ? order[k] : 0u;
+    // A heavy bucket's entries hold counts.  Whatever index they spell, it is
+    // clamped, and the bucket that it leads to is heavy or does not hold k.
+    const int i = min((int)(mine & kIndexMask), n - 1);
     const int key = keys[i];
     const int b = start[key >> drop], e = start[(key >> drop) + 1];
-    const int last = min(kWave, n - k0) - 1;
-    const int lo = __shfl(b, 0), hi = __shfl(e, last);
+    const bool live = k < n && b <= k && k < e && e - b < heavy;
+    // a heavy bucket is longer than a wave: the live lanes are consecutive
+    const uint64_t lanes = __ballot(live);
+    if (!lanes) return;
+    const int lo = __shfl(b, __ffsll((unsigned long long)lanes) - 1);
+    const int hi = __shfl(e, 63 - __clzll((long long)lanes));
     const bool one = __ballot(live && (b != lo || e != hi)) == 0ull;
     unsigned* sh = entries[w];
     int r = 0;
@@ -586,8 +799,9 @@ constexpr int kOwnCarryBlocks = 2048;
 hipError_t launch_cell_keys(const double* pos, const float* mass, int n,
                             Geom g, int* keys, float4* rec, hipStream_t st) {
     if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_cell_keys, dim3(blocks_for(n, kBlock)), dim3(kBlock),
-                       0, st, pos, mass, n, g, keys, (int*)nullptr, rec, (int*)nullptr, 0);
+    hipLaunchKernelGGL(k_cell_keys<kNoCounts>, dim3(blocks_for(n, kBlock)), dim3(kBlock),
+                       0, st, pos, mass, n, g, keys, (int*)nullptr, rec, (int*)nullptr, 0,
+                       (unsigned*)nullptr);
     return hipGetLastError();
 }
 
@@ -607,7 +821,7 @@ size_t scan_tmp_ints(int n) {
 
 namespace {
 hipError_t scan_exclusive(const int* in, int* out, int n, int* tmp, int* heads, int every,
-                          hipStream_t st) {
+                          int* large, int least, hipStream_t st) {
     if (n <= 0) return hipSuccess;
     const dim3 block(kBlock);
     if (few_items(n)) {
@@ -615,7 +829,7 @@ hipError_t scan_exclusive(const int* in, int* out, int n, int* tmp, int* heads, 
         if (nb > 1)
             hipLaunchKernelGGL(k_scan_reduce<kFewItems>, dim3(nb), block, 0, st, in, n, tmp);
         hipLaunchKernelGGL(k_scan_apply<kFewItems>, dim3(nb), block, 0, st, in, out, n,
-                           (const int*)tmp, false, heads, every);
+                           (const int*)tmp, false, heads, every, large, least);
         return hipGetLastError();
     }
     const int nb = blocks_for(n, kTile);
@@ -623,20 +837,20 @@ hipError_t scan_exclusive(const int* in, int* out, int n, int* tmp, int* heads, 
     hipLaunchKernelGGL(k_scan_reduce<kItems>, dim3(nb), block, 0, st, in, n, tmp);
     if (scanned) hipLaunchKernelGGL(k_scan_single, dim3(1), block, 0, st, tmp, nb);
     hipLaunchKernelGGL(k_scan_apply<kItems>, dim3(nb), block, 0, st, in, out, n,
-                       (const int*)tmp, scanned, heads, every);
+                       (const int*)tmp, scanned, heads, every, large, least);
     return hipGetLastError();
 }
 }  // namespace
 
 hipError_t launch_scan_exclusive(const int* in, int* out, int n, int* tmp,
                                  hipStream_t st) {
-    return scan_exclusive(in, out, n, tmp, nullptr, 0, st);
+    return scan_exclusive(in, out, n, tmp, nullptr, 0, nullptr, 0, st);
 }
 
 hipError_t launch_counting_sort(const double* pos, const float* mass, int n, Geom g,
                                 int sub, int* keys, int* arrival, float4* rec_in,
                                 int* buckets, int* cell_start, int* tmp, unsigned* order,
-                                float4* rec, int* perm, int* keys_out,
+                                int* any_heavy, float4* rec, int* perm, int* keys_out,
                                 const WorkBuffers* work, hipStream_t st) {
     static_assert(kBlock == kWorkBlock, "both shares of a launch have the same blocks");
     static_assert(kOneListParticles >= kCountingParticles, "the histogram needs no XCDs");
@@ -645,24 +859,31 @@ hipError_t launch_counting_sort(const double* pos, const float* mass, int n, Geo
     const int ncell = g.N * g.N * g.N;
     const int nbuckets = ncell << sub;
     const int nb = blocks_for(n, kBlock);
-    const int clear = work ? std::max(nbuckets + 1, kControlInts) : nbuckets + 1;
-    hipLaunchKernelGGL(k_clear_two, dim3(blocks_for(clear, kBlock)), dim3(kBlock), 0, st,
-                       buckets, nbuckets + 1,
-                       work ? reinterpret_cast<int*>(work->ctl) : nullptr,
-                       work ? kControlInts : 0);
-    hipLaunchKernelGGL(k_cell_keys, dim3(nb), dim3(kBlock), 0, st, pos, mass, n, g, keys,
-                       arrival, rec_in, buckets, drop);
+    const int heavy = heavy_least(n, drop);
+    // the work list's control words hold any_heavy
+    int* words = work ? reinterpret_cast<int*>(work->ctl) : any_heavy;
+    const int nwords = work ? kControlInts : 1;
+    hipLaunchKernelGGL(k_clear_two, dim3(blocks_for(std::max(nbuckets + 1, nwords), kBlock)),
+                       dim3(kBlock), 0, st, buckets, nbuckets + 1, words, nwords);
+    unsigned* zero = n >= heavy ? order : nullptr;
+    if (n <= kCountEachParticles)
+        hipLaunchKernelGGL(k_cell_keys<kCountEach>, dim3(nb), dim3(kBlock), 0, st, pos, mass, n,
+                           g, keys, arrival, rec_in, buckets, drop, zero);
+    else
+        hipLaunchKernelGGL(k_cell_keys<kCountBlock>, dim3(nb), dim3(kBlock), 0, st, pos, mass, n,
+                           g, keys, arrival, rec_in, buckets, drop, zero);
     hipError_t e = scan_exclusive(buckets, buckets, nbuckets + 1, tmp,
-                                  buckets == cell_start ? nullptr : cell_start, sub, st);
+                                  buckets == cell_start ? nullptr : cell_start, sub,
+                                  n >= heavy ? any_heavy : nullptr, heavy, st);
     if (e != hipSuccess) return e;
     const BesideWork beside{CellUnits{cell_start, g}, work ? *work : WorkBuffers{}, nb};
     hipLaunchKernelGGL(k_place, dim3(nb + (work ? window_blocks(g.N) : 0)), dim3(kBlock), 0, st,
                        (const int*)keys, (const int*)arrival, (const int*)buckets, n, drop,
-                       order, beside);
+                       heavy, order, (const int*)any_heavy, beside);
     hipLaunchKernelGGL(k_order_gather, dim3(nb + (work ? blocks_for(ncell, kBlock) : 0)),
                        dim3(kBlock), 0, st, (const unsigned*)order, (const int*)buckets,
-                       (const int*)keys, n, drop, (const float4*)rec_in, rec, perm, keys_out,
-                       beside);
+                       (const int*)keys, n, drop, heavy, (const int*)any_heavy,
+                       (const float4*)rec_in, rec, perm, keys_out, beside);
     return hipGetLastError();
 }
 

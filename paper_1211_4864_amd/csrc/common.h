@@ -71,7 +71,7 @@ constexpr int kMaxSplitItems = 2 * kResidentWaves;
 struct WorkControl {
     unsigned long long pairs;             // pair work of all units
     int n_items;
-    int pad;
+    int any_heavy;                        // counting sort: a heavy bucket was met
     int count[kXcds * kCostBuckets];      // items per (list, cost bucket)
     int taken[kXcds * kCostBuckets];      // ranks handed out to blocks
 };
@@ -101,11 +101,12 @@ constexpr int kOneListParticles = kCountingParticles;
 // The sort's entries hold the input index in their low bits.
 constexpr int kCountingIndexBits = 26;
 // buckets: (cells << sub) + 1 counters, cell_start itself when sub is 0.
+// any_heavy: that word of the work list's control, whether or not work is given.
 // work: also form the work list's windows and histogram there (or null).
 hipError_t launch_counting_sort(const double* pos, const float* mass, int n, Geom g,
                                 int sub, int* keys, int* arrival, float4* rec_in,
                                 int* buckets, int* cell_start, int* tmp, unsigned* order,
-                                float4* rec, int* perm, int* keys_out,
+                                int* any_heavy, float4* rec, int* perm, int* keys_out,
                                 const WorkBuffers* work, hipStream_t st);
 size_t scan_tmp_ints(int n);
 hipError_t launch_scan_exclusive(const int* in, int* out, int n, int* tmp,
