@@ -258,13 +258,19 @@ WorkBuffers work_buffers(const Layout& L) {
                        ws_at<unsigned long long>(L.col_cost), ws_at<int>(L.col_xcd)};
 }
 
-// Bins into the workspace; returns (through the pointers) where cell_start,
-// the permutation and the sorted records ended up.  then_worklist: the caller
-// builds the work list of these cells next (worklist_impl).
+// What a binning left in the workspace beside cell_start and the records.
+struct Binned {
+    int* perm = nullptr;
+    int* keys = nullptr;         // sorted
+    int* spare = nullptr;        // n ints that nothing needs any more
+    bool work_started = false;   // the work list's windows and histogram are there
+};
+
+// Bins into the workspace.  with_work: the work list of these cells follows
+// (worklist_impl), and what the sort's launches can do for it, they do.
 int bin_impl(const double* pos, const float* mass, int64_t n, const Geom& g,
-             const Layout& L, int* cell_start, int** perm_out, float4* rec,
-             int* perm_user, int** keys_out = nullptr, int** spare_out = nullptr,
-             bool then_worklist = false) {
+             const Layout& L, int* cell_start, float4* rec, int* perm_user, bool with_work,
+             Binned* out) {
     const int nn = (int)n;
     int* ka = ws_at<int>(L.keys_a);
     int* va = ws_at<int>(L.vals_a);
@@ -274,40 +280,29 @@ int bin_impl(const double* pos, const float* mass, int64_t n, const Geom& g,
     int* tmp = ws_at<int>(L.scan_tmp);
     float4* rec_in = ws_at<float4>(L.gsorted);
     if (L.count_sub >= 0) {
-        // keys_a: keys in input order; keys_b: order of arrival, then free;
+        // keys_a: keys in input order, then free; keys_b: order of arrival;
         // vals_a: place of arrival, then the sorted keys; vals_b: permutation
         const WorkBuffers work = work_buffers(L);
         HIP_TRY(launch_counting_sort(pos, mass, nn, g, L.count_sub, ka, va, rec_in,
                                      L.count_sub ? hist : cell_start, cell_start, tmp,
                                      reinterpret_cast<unsigned*>(kb), &work.ctl->any_heavy,
-                                     rec, vb, va,
-                                     then_worklist ? &work : nullptr, g_stream));
-        std::swap(va, vb);
-        std::swap(ka, vb);
-        if (perm_user) {
-            HIP_TRY(hipMemcpyAsync(perm_user, va, sizeof(int) * (size_t)nn,
-                                   hipMemcpyDeviceToDevice, g_stream));
+                                     rec, vb, va, with_work ? &work : nullptr, g_stream));
+        *out = Binned{vb, va, ka, with_work};
+    } else {
+        HIP_TRY(launch_cell_keys(pos, mass, nn, g, ka, rec_in, g_stream));
+        for (int p = 0; p < L.passes; ++p) {
+            HIP_TRY(launch_radix_pass(ka, p ? va : nullptr, kb, vb, nn, L.digit_bits * p,
+                                      L.digit_bits, hist, tmp, g_stream));
+            std::swap(ka, kb);
+            std::swap(va, vb);
         }
-        *perm_out = va;
-        if (keys_out) *keys_out = ka;
-        if (spare_out) *spare_out = vb;
-        return HACC_SR_OK;
+        HIP_TRY(launch_gather_records(rec_in, va, ka, nn, g, rec, cell_start, g_stream));
+        *out = Binned{va, ka, vb, false};
     }
-    HIP_TRY(launch_cell_keys(pos, mass, nn, g, ka, rec_in, g_stream));
-    for (int p = 0; p < L.passes; ++p) {
-        HIP_TRY(launch_radix_pass(ka, p ? va : nullptr, kb, vb, nn, L.digit_bits * p,
-                                  L.digit_bits, hist, tmp, g_stream));
-        std::swap(ka, kb);
-        std::swap(va, vb);
-    }
-    HIP_TRY(launch_gather_records(rec_in, va, ka, nn, g, rec, cell_start, g_stream));
     if (perm_user) {
-        HIP_TRY(hipMemcpyAsync(perm_user, va, sizeof(int) * (size_t)nn,
+        HIP_TRY(hipMemcpyAsync(perm_user, out->perm, sizeof(int) * (size_t)nn,
                                hipMemcpyDeviceToDevice, g_stream));
     }
-    *perm_out = va;
-    if (keys_out) *keys_out = ka;
-    if (spare_out) *spare_out = vb;
     return HACC_SR_OK;
 }
 
@@ -358,12 +353,13 @@ int check_leaf_max(int32_t leaf_max) {
 }
 
 
-// Builds the cost-ordered work list; returns the device counter of items.
+// Builds the cost-ordered work list of a binning's cells; returns the device
+// counter of items.
 int worklist_impl(const int* cell_start, int64_t n, const Geom& g, const Layout& L,
-                  const WorkItem** items_out, const int** n_items_dev) {
+                  const Binned& bn, const WorkItem** items_out, const int** n_items_dev) {
     WorkItem* items = ws_at<WorkItem>(L.items);
     const WorkBuffers b = work_buffers(L);
-    HIP_TRY(launch_worklist(cell_start, (int)n, g, L.count_sub >= 0, L.max_items, b, items,
+    HIP_TRY(launch_worklist(cell_start, (int)n, g, bn.work_started, L.max_items, b, items,
                             g_stream));
     *items_out = items;
     *n_items_dev = &b.ctl->n_items;
@@ -376,27 +372,26 @@ int rcb_prepare(const double* pos, const float* mass, int64_t n, const Geom& g,
                 const WorkItem** items, const int** nitems, int* grid) {
     int* cs = ws_at<int>(L.counts);
     float4* rec = ws_at<float4>(L.rec);
-    int *perm = nullptr, *keys = nullptr, *spare = nullptr;
+    Binned bn;
     const int* nl_dev = nullptr;
     int rc = timed(2, [&] {
-        int r = bin_impl(pos, mass, n, g, L, cs, &perm, rec, nullptr, &keys, &spare);
-        if (r != HACC_SR_OK) return r;
-        return HACC_SR_OK;
+        return bin_impl(pos, mass, n, g, L, cs, rec, nullptr, false, &bn);
     });
     if (rc != HACC_SR_OK) return rc;
     rc = timed(6, [&] {
-        return rcb_impl(n, g, L, cs, rec, perm, spare, leaf_max, nullptr, nullptr, &nl_dev);
+        return rcb_impl(n, g, L, cs, rec, bn.perm, bn.spare, leaf_max, nullptr, nullptr,
+                        &nl_dev);
     });
     if (rc != HACC_SR_OK) return rc;
     if (grad_acc) {
         // the cotangents follow the final (RCB) order
-        HIP_TRY(launch_gather_vec3(grad_acc, perm, (int)n, ws_at<float4>(L.gsorted),
+        HIP_TRY(launch_gather_vec3(grad_acc, bn.perm, (int)n, ws_at<float4>(L.gsorted),
                                    g_stream));
     }
     rc = timed(3, [&] {
-        return worklist_rcb_impl(n, cs, keys, g, L, nl_dev, items, nitems, grid);
+        return worklist_rcb_impl(n, cs, bn.keys, g, L, nl_dev, items, nitems, grid);
     });
-    *perm_out = perm;
+    *perm_out = bn.perm;
     return rc;
 }
 
@@ -413,16 +408,16 @@ int force_into(const double* pos, const float* mass, int64_t n, const Geom& g,
                const PairParams& P, const Layout& L, float* out_acc, int** perm_out = nullptr) {
     int* cs = ws_at<int>(L.counts);
     float4* rec = ws_at<float4>(L.rec);
-    int* perm = nullptr;
-    int rc = timed(2, [&] { return bin_impl(pos, mass, n, g, L, cs, &perm, rec, nullptr, nullptr, nullptr, true); });
+    Binned bn;
+    int rc = timed(2, [&] { return bin_impl(pos, mass, n, g, L, cs, rec, nullptr, true, &bn); });
     if (rc != HACC_SR_OK) return rc;
     const WorkItem* items;
     const int* nitems;
-    rc = timed(3, [&] { return worklist_impl(cs, n, g, L, &items, &nitems); });
+    rc = timed(3, [&] { return worklist_impl(cs, n, g, L, bn, &items, &nitems); });
     if (rc != HACC_SR_OK) return rc;
-    if (perm_out) *perm_out = perm;
+    if (perm_out) *perm_out = bn.perm;
     return timed(0, [&] {
-        HIP_TRY(launch_pair_force(items, L.max_items, nitems, rec, cs, perm, g,
+        HIP_TRY(launch_pair_force(items, L.max_items, nitems, rec, cs, bn.perm, g,
                                   P, out_acc, g_stream));
         return HACC_SR_OK;
     });
@@ -493,13 +488,12 @@ int hacc_sr_force_noalloc(const double* pos, const float* mass, int64_t n, doubl
     // zero is cleared by a fill kernel, so earlier contents do not matter
     int* cs = ws_at<int>(L.counts);
     float4* rec = ws_at<float4>(L.rec);
-    int* perm = nullptr;
-    if ((rc = bin_impl(pos, mass, n, g, L, cs, &perm, rec, nullptr, nullptr, nullptr, true)) != HACC_SR_OK)
-        return rc;
+    Binned bn;
+    if ((rc = bin_impl(pos, mass, n, g, L, cs, rec, nullptr, true, &bn)) != HACC_SR_OK) return rc;
     const WorkItem* items;
     const int* nitems;
-    if ((rc = worklist_impl(cs, n, g, L, &items, &nitems)) != HACC_SR_OK) return rc;
-    HIP_TRY(launch_pair_force(items, L.max_items, nitems, rec, cs, perm, g, P, out_acc,
+    if ((rc = worklist_impl(cs, n, g, L, bn, &items, &nitems)) != HACC_SR_OK) return rc;
+    HIP_TRY(launch_pair_force(items, L.max_items, nitems, rec, cs, bn.perm, g, P, out_acc,
                               g_stream));
     return HACC_SR_OK;
 }
@@ -573,9 +567,9 @@ int hacc_sr_bin(const double* pos, const float* mass, int64_t n, double box,
             HIP_TRY(launch_fill_i32(cell_start, (int)(L.ncell + 1), 0, g_stream));
             return HACC_SR_OK;
         }
-        int* p;
-        return bin_impl(pos, mass, n, g, L, cell_start, &p,
-                        reinterpret_cast<float4*>(sorted_rec), perm);
+        Binned bn;
+        return bin_impl(pos, mass, n, g, L, cell_start, reinterpret_cast<float4*>(sorted_rec),
+                        perm, false, &bn);
     });
 }
 
@@ -654,24 +648,24 @@ int hacc_sr_force_vjp(const double* pos, const float* mass, int64_t n,
     int* cs = ws_at<int>(L.counts);
     float4* rec = ws_at<float4>(L.rec);
     float4* gs = ws_at<float4>(L.gsorted);
-    int* perm = nullptr;
+    Binned bn;
     rc = timed(2, [&] {
-        const int r = bin_impl(pos, mass, n, g, L, cs, &perm, rec, nullptr, nullptr, nullptr, true);
+        const int r = bin_impl(pos, mass, n, g, L, cs, rec, nullptr, true, &bn);
         if (r != HACC_SR_OK) return r;
-        HIP_TRY(launch_gather_vec3(grad_acc, perm, (int)n, gs, g_stream));
+        HIP_TRY(launch_gather_vec3(grad_acc, bn.perm, (int)n, gs, g_stream));
         return HACC_SR_OK;
     });
     if (rc != HACC_SR_OK) return rc;
     const WorkItem* items;
     const int* nitems;
-    rc = timed(3, [&] { return worklist_impl(cs, n, g, L, &items, &nitems); });
+    rc = timed(3, [&] { return worklist_impl(cs, n, g, L, bn, &items, &nitems); });
     if (rc != HACC_SR_OK) return rc;
     rc = timed(1, [&] {
-        HIP_TRY(launch_pair_vjp(items, L.max_items, nitems, rec, gs, cs, perm, g,
+        HIP_TRY(launch_pair_vjp(items, L.max_items, nitems, rec, gs, cs, bn.perm, g,
                                 P, out_grad_pos, g_stream));
         return HACC_SR_OK;
     });
-    if (rc == HACC_SR_OK) keep_binning(n, box, r_cut, perm);
+    if (rc == HACC_SR_OK) keep_binning(n, box, r_cut, bn.perm);
     return rc;
 }
 
@@ -750,19 +744,19 @@ int hacc_sr_rcb_bin(const double* pos, const float* mass, int64_t n, double box,
         }
         int* cs = ws_at<int>(L.counts);
         float4* rec = ws_at<float4>(L.rec);
-        int *p = nullptr, *spare = nullptr;
-        int r = bin_impl(pos, mass, n, g, L, cs, &p, rec, nullptr, nullptr, &spare);
+        Binned bn;
+        int r = bin_impl(pos, mass, n, g, L, cs, rec, nullptr, false, &bn);
         if (r != HACC_SR_OK) return r;
         const int* nl_dev = nullptr;
-        r = rcb_impl(n, g, L, cs, rec, p, spare, leaf_max,
+        r = rcb_impl(n, g, L, cs, rec, bn.perm, bn.spare, leaf_max,
                      want_nodes ? reinterpret_cast<int4*>(nodes) : nullptr, node_split,
                      &nl_dev);
         if (r != HACC_SR_OK) return r;
         const int nn = (int)n;
         HIP_TRY(hipMemcpyAsync(cell_start, cs, sizeof(int) * (size_t)(L.ncell + 1),
                                hipMemcpyDeviceToDevice, g_stream));
-        HIP_TRY(hipMemcpyAsync(perm, p, sizeof(int) * (size_t)nn, hipMemcpyDeviceToDevice,
-                               g_stream));
+        HIP_TRY(hipMemcpyAsync(perm, bn.perm, sizeof(int) * (size_t)nn,
+                               hipMemcpyDeviceToDevice, g_stream));
         HIP_TRY(hipMemcpyAsync(sorted_rec, rec, sizeof(float4) * (size_t)nn,
                                hipMemcpyDeviceToDevice, g_stream));
         HIP_TRY(hipMemcpyAsync(n_leaves, nl_dev, sizeof(int), hipMemcpyDeviceToDevice,
@@ -850,11 +844,11 @@ int hacc_sr_force_plain(const double* pos, const float* mass, int64_t n,
     if ((rc = check_ws(L)) != HACC_SR_OK) return rc;
     int* cs = ws_at<int>(L.counts);
     float4* rec = ws_at<float4>(L.rec);
-    int *perm = nullptr, *keys = nullptr;
-    rc = bin_impl(pos, mass, n, g, L, cs, &perm, rec, nullptr, &keys);
+    Binned bn;
+    rc = bin_impl(pos, mass, n, g, L, cs, rec, nullptr, false, &bn);
     if (rc != HACC_SR_OK) return rc;
     return timed(4, [&] {
-        HIP_TRY(launch_force_plain(rec, keys, cs, perm, (int)n, g,
+        HIP_TRY(launch_force_plain(rec, bn.keys, cs, bn.perm, (int)n, g,
                                    P, out_acc,
                                    g_stream));
         return HACC_SR_OK;
@@ -879,12 +873,12 @@ int hacc_sr_force_vjp_plain(const double* pos, const float* mass, int64_t n,
     int* cs = ws_at<int>(L.counts);
     float4* rec = ws_at<float4>(L.rec);
     float4* gs = ws_at<float4>(L.gsorted);
-    int *perm = nullptr, *keys = nullptr;
-    rc = bin_impl(pos, mass, n, g, L, cs, &perm, rec, nullptr, &keys);
+    Binned bn;
+    rc = bin_impl(pos, mass, n, g, L, cs, rec, nullptr, false, &bn);
     if (rc != HACC_SR_OK) return rc;
-    HIP_TRY(launch_gather_vec3(grad_acc, perm, (int)n, gs, g_stream));
+    HIP_TRY(launch_gather_vec3(grad_acc, bn.perm, (int)n, gs, g_stream));
     return timed(5, [&] {
-        HIP_TRY(launch_vjp_plain(rec, gs, keys, cs, perm, (int)n, g,
+        HIP_TRY(launch_vjp_plain(rec, gs, bn.keys, cs, bn.perm, (int)n, g,
                                  P, out_grad_pos,
                                  g_stream));
         return HACC_SR_OK;
@@ -956,12 +950,12 @@ int hacc_sr_count_pairs(const double* pos, int64_t n, double box, float r_cut,
     if (n == 0) return HACC_SR_OK;
     int* cs = ws_at<int>(L.counts);
     float4* rec = ws_at<float4>(L.rec);
-    int* perm = nullptr;
-    rc = bin_impl(pos, nullptr, n, g, L, cs, &perm, rec, nullptr, nullptr, nullptr, true);
+    Binned bn;
+    rc = bin_impl(pos, nullptr, n, g, L, cs, rec, nullptr, true, &bn);
     if (rc != HACC_SR_OK) return rc;
     const WorkItem* items;
     const int* nitems;
-    if ((rc = worklist_impl(cs, n, g, L, &items, &nitems)) != HACC_SR_OK) return rc;
+    if ((rc = worklist_impl(cs, n, g, L, bn, &items, &nitems)) != HACC_SR_OK) return rc;
     HIP_TRY(launch_pair_count(items, L.max_items, nitems, rec, cs, g, P,
                               reinterpret_cast<unsigned long long*>(out_counts),
                               g_stream));
