@@ -80,6 +80,13 @@ int key_bits(int64_t ncell) {
 }
 
 
+// The documented size limit of the entry points: twice the units of targets
+// (cells, or leaves, of which there are at most n) and n / 64 below 2^31.
+// item_bound, which the work list is sized with, is at most n and always fits.
+bool too_many_units(int64_t units, int64_t n) {
+    return 2 * units + n / kItemI + 1 > (int64_t)INT32_MAX;
+}
+
 // Validates (n, box, r_cut) and derives the chaining-mesh geometry.
 int make_geom(int64_t n, double box, float r_cut, Geom* g) {
     if (n < 0 || !is_fin(box) || box == 0.0 || !is_fin(r_cut) || !(r_cut > 0.0f))
@@ -93,10 +100,7 @@ int make_geom(int64_t n, double box, float r_cut, Geom* g) {
     int N = (int)Nd;
     while (N > 1 && b / N < (double)r_cut) --N;
     if (box > 0.0 && N < 3) return HACC_SR_EDOMAIN;
-    // the work list's capacity (see layout_for) must fit an int
-    const int64_t ncell = (int64_t)N * N * N;
-    if (2 * std::min<int64_t>(n, ncell) + n / kItemI + 1 > (int64_t)INT32_MAX)
-        return HACC_SR_EDOMAIN;
+    if (too_many_units(std::min<int64_t>(n, (int64_t)N * N * N), n)) return HACC_SR_EDOMAIN;
     g->N = N;
     g->periodic = box > 0.0 ? 1 : 0;
     g->box = b;
@@ -176,9 +180,6 @@ int item_bound(int64_t units, int64_t n) {
     return (int)std::max<int64_t>(
         1, std::min(n, 2 * units + n / kItemI + 1 + kMaxSplitItems));
 }
-
-// Unsplit items of the RCB work list: at most n leaves.
-int64_t rcb_item_bound(int64_t n) { return 2 * n + n / kItemI + 1; }
 
 // Counting sort of small sets: its buckets are cells, or their 2^3 or 4^3
 // sub-cells as long as that makes at most four per particle.
@@ -713,7 +714,7 @@ int hacc_sr_workspace_bytes_rcb(int64_t n, double box, float r_cut, size_t* byte
     Geom g;
     const int rc = make_geom(n, box, r_cut, &g);
     if (rc != HACC_SR_OK) return rc;
-    if (rcb_item_bound(n) > (int64_t)INT32_MAX) return HACC_SR_EDOMAIN;
+    if (too_many_units(n, n)) return HACC_SR_EDOMAIN;
     *bytes = layout_for(n, g, true).total;
     return HACC_SR_OK;
 }
@@ -727,7 +728,7 @@ int hacc_sr_rcb_bin(const double* pos, const float* mass, int64_t n, double box,
     int rc = make_geom(n, box, r_cut, &g);
     if (rc != HACC_SR_OK) return rc;
     if ((rc = check_leaf_max(leaf_max)) != HACC_SR_OK) return rc;
-    if (rcb_item_bound(n) > (int64_t)INT32_MAX) return HACC_SR_EDOMAIN;
+    if (too_many_units(n, n)) return HACC_SR_EDOMAIN;
     if (!cell_start || !leaf_start || !n_leaves) return HACC_SR_EINVAL;
     if (n > 0 && (!pos || !mass || !perm || !sorted_rec)) return HACC_SR_EINVAL;
     const bool want_nodes = nodes || node_split || n_nodes;
@@ -782,7 +783,7 @@ int hacc_sr_force_rcb(const double* pos, const float* mass, int64_t n, double bo
     PairParams P;
     if ((rc = make_params(r_cut, eps, poly, &P)) != HACC_SR_OK) return rc;
     if ((rc = check_leaf_max(leaf_max)) != HACC_SR_OK) return rc;
-    if (rcb_item_bound(n) > (int64_t)INT32_MAX) return HACC_SR_EDOMAIN;
+    if (too_many_units(n, n)) return HACC_SR_EDOMAIN;
     if (n > 0 && (!pos || !mass || !out_acc)) return HACC_SR_EINVAL;
     if (n == 0) return HACC_SR_OK;
     const Layout L = layout_for(n, g, true);
@@ -810,7 +811,7 @@ int hacc_sr_force_vjp_rcb(const double* pos, const float* mass, int64_t n, doubl
     PairParams P;
     if ((rc = make_params(r_cut, eps, poly, &P)) != HACC_SR_OK) return rc;
     if ((rc = check_leaf_max(leaf_max)) != HACC_SR_OK) return rc;
-    if (rcb_item_bound(n) > (int64_t)INT32_MAX) return HACC_SR_EDOMAIN;
+    if (too_many_units(n, n)) return HACC_SR_EDOMAIN;
     if (n > 0 && (!pos || !mass || !grad_acc || !out_grad_pos)) return HACC_SR_EINVAL;
     if (n == 0) return HACC_SR_OK;
     const Layout L = layout_for(n, g, true);

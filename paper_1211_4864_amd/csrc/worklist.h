@@ -12,8 +12,8 @@ namespace {
 constexpr int kWorkBlock = 256;
 constexpr int kOrderBuckets = kXcds * kCostBuckets;
 
-__device__ __forceinline__ int floor_pow2(int v) {
-    return v <= 0 ? 0 : (1 << (31 - __clz(v)));
+__host__ __device__ __forceinline__ int floor_pow2(int v) {
+    return v <= 0 ? 0 : (1 << (31 - __builtin_clz((unsigned)v)));
 }
 
 // Unit of targets that share one source window.
@@ -66,7 +66,7 @@ struct LeafUnits {
 
 // Sources of a unit's window, estimated from its first cell's 27-cell window.
 __device__ __forceinline__ int unit_window(const Unit& u, const int* cell_window) {
-    return (int)((int64_t)cell_window[u.key] * (u.zlen + 2) / 3);
+    return (int)min((int64_t)cell_window[u.key] * (u.zlen + 2) / 3, (int64_t)INT32_MAX);
 }
 
 // Step limit of an item: the steps (64 target x source pairs) that one of the
@@ -79,31 +79,32 @@ __device__ __forceinline__ int unit_window(const Unit& u, const int* cell_window
 // of 4096 24 -> 18).
 // The items this adds are bounded: a unit of c targets and window w gets at
 // most c / 32 * w / limit + 2, so all units together at most
-// 2 * steps / limit <= 2 * kResidentWaves more than unsplit.
-__device__ __forceinline__ int item_limit(unsigned long long pairs) {
+// 2 * steps / limit <= 2 * kResidentWaves more than unsplit.  That needs
+// limit >= share: a share that does not fit an int (pairs >= 2^50) becomes
+// INT32_MAX, which no window exceeds, so that nothing is split.
+__host__ __device__ __forceinline__ int item_limit(unsigned long long pairs) {
     const unsigned long long share =
         pairs / ((unsigned long long)kItemI * kResidentWaves) + 1;
-    const unsigned long long least =
-        min(max(8 * share, (unsigned long long)kFewestSteps), (unsigned long long)kMinSteps);
-    return (int)min(max(share, least), 0x0fffffffull);
+    unsigned long long least = 8 * share;
+    if (least < kFewestSteps) least = kFewestSteps;
+    if (least > kMinSteps) least = kMinSteps;
+    const unsigned long long limit = share > least ? share : least;
+    return limit < INT32_MAX ? (int)limit : INT32_MAX;
 }
 
-__device__ __forceinline__ int item_size(int window, int limit) {
+__host__ __device__ __forceinline__ int item_size(int window, int limit) {
     int t = kItemI;
-    while (t > 1 && window > limit) {
-        t >>= 1;
-        limit <<= 1;
-    }
+    for (int64_t steps = limit; t > 1 && window > steps; steps <<= 1) t >>= 1;
     return t;
 }
 
 // Items of a unit: `full` of T targets, then one of p and one of q (0: none).
 struct Pieces {
     int T, full, p, q;
-    __device__ __forceinline__ int items() const { return full + (p > 0) + (q > 0); }
+    __host__ __device__ __forceinline__ int items() const { return full + (p > 0) + (q > 0); }
 };
 
-__device__ __forceinline__ Pieces pieces_of(int count, int T) {
+__host__ __device__ __forceinline__ Pieces pieces_of(int count, int T) {
     Pieces s;
     s.T = T;
     s.full = count / T;
