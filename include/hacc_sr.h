@@ -84,7 +84,12 @@ int hacc_sr_set_stream(void *stream);
 /* Chaining-mesh cells per axis for (box, r_cut): N = floor(|box| / r_cut). */
 int hacc_sr_grid_dim(double box, float r_cut, int32_t *cells_per_axis);
 
-/* Workspace bytes needed by any entry point for n particles. */
+/* Workspace bytes needed by any entry point for n particles.  Sets of at most
+ * 2^19 particles sort them by sub-cells of their cells, whose counters are part
+ * of it (up to 16 bytes per particle); a workspace that holds all but those is
+ * accepted too and sorts by fewer, with the same results.  Below that,
+ * HACC_SR_ENOSPACE.  The size is this library version's: query it rather than
+ * keep it. */
 int hacc_sr_workspace_bytes(int64_t n, double box, float r_cut, size_t *bytes);
 
 /* Register caller-owned device memory as the workspace (256-byte aligned).

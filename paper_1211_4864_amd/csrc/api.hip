@@ -182,15 +182,18 @@ int item_bound(int64_t units, int64_t n) {
 }
 
 // Counting sort of small sets: its buckets are cells, or their 2^3 or 4^3
-// sub-cells as long as that makes at most four per particle.
-int counting_sub_bits(int64_t n, int64_t ncell, int sbits) {
+// sub-cells as long as that makes at most four per particle; 2^3 at most in the
+// compact layout.  The binning is the same whichever they are.
+int counting_sub_bits(int64_t n, int64_t ncell, int sbits, bool compact) {
     if (n > kCountingParticles) return -1;
+    const int most = compact ? std::min(sbits, 3) : sbits;
     int sub = 0;
-    while (sub + 3 <= sbits && (ncell << (sub + 3)) <= 4 * n) sub += 3;
+    while (sub + 3 <= most && (ncell << (sub + 3)) <= 4 * n) sub += 3;
     return sub;
 }
 
-Layout layout_for(int64_t n, const Geom& g, bool rcb = false) {
+// compact: for a workspace that is too small for the usual layout (layout_in).
+Layout layout_for(int64_t n, const Geom& g, bool rcb = false, bool compact = false) {
     Layout L{};
     const int nn = (int)n;
     L.rcb = rcb;
@@ -202,7 +205,7 @@ Layout layout_for(int64_t n, const Geom& g, bool rcb = false) {
     L.digit_bits = std::min(kMaxDigitBits, std::max(8, (bits + 2) / 3));
     L.passes = (bits + L.digit_bits - 1) / L.digit_bits;
     int64_t hist_n = ((int64_t)1 << L.digit_bits) * L.radix_nb;
-    L.count_sub = counting_sub_bits(n, L.ncell, g.sbits);
+    L.count_sub = counting_sub_bits(n, L.ncell, g.sbits, compact);
     if (L.count_sub > 0)
         hist_n = std::max(hist_n, (L.ncell << L.count_sub) + 1);
     int64_t scan_n = std::max<int64_t>(hist_n, L.ncell + 1);
@@ -214,18 +217,29 @@ Layout layout_for(int64_t n, const Geom& g, bool rcb = false) {
         return at;
     };
     const size_t ni = sizeof(int) * (size_t)std::max<int64_t>(n, 1);
+    // the permutation ends up in vals_b, after an even number of radix passes
+    // in vals_a; of the sort's other buffers only the RCB leaves need any
+    // afterwards, so that elsewhere the work items take their place
+    const bool in_a = L.count_sub < 0 && L.passes % 2 == 0;
+    (in_a ? L.vals_a : L.vals_b) = take(ni);
+    const size_t sort_at = off;
     L.keys_a = take(ni);
-    L.vals_a = take(ni);
     L.keys_b = take(ni);
-    L.vals_b = take(ni);
-    L.counts = take(sizeof(int) * (size_t)(L.ncell + 1));
+    (in_a ? L.vals_b : L.vals_a) = take(ni);
     L.hist = take(sizeof(int) * (size_t)hist_n);
     L.scan_tmp = take(sizeof(int) * scan_tmp_ints((int)scan_n));
+    const size_t items_bytes = sizeof(WorkItem) * (size_t)L.max_items;
+    if (rcb) {
+        L.items = take(items_bytes);
+    } else {
+        L.items = sort_at;
+        off = std::max(off, align_up(sort_at + items_bytes));
+    }
+    L.counts = take(sizeof(int) * (size_t)(L.ncell + 1));
     L.rec = take(sizeof(float4) * (size_t)std::max<int64_t>(n, 1));
     // also holds the records in input order during binning (the sorted
     // cotangents are gathered only after the records)
     L.gsorted = take(sizeof(float4) * (size_t)std::max<int64_t>(n, 1));
-    L.items = take(sizeof(WorkItem) * (size_t)L.max_items);
     L.work_ctl = take(sizeof(WorkControl));
     L.cell_window = take(sizeof(int) * (size_t)L.ncell);
     L.col_cost = take(sizeof(unsigned long long) * (size_t)(g.N) * (size_t)g.N);
@@ -248,9 +262,16 @@ T* ws_at(size_t off) {
     return reinterpret_cast<T*>(base + off);
 }
 
-int check_ws(const Layout& L) {
-    if (!g_ws || g_ws_bytes < L.total) return HACC_SR_ENOSPACE;
-    return HACC_SR_OK;
+// Layout for a workspace of `bytes`: the usual one, the compact one where only
+// that fits.  Returns HACC_SR_ENOSPACE if neither does.
+int layout_in(size_t bytes, int64_t n, const Geom& g, bool rcb, Layout* L) {
+    *L = layout_for(n, g, rcb);
+    if (bytes < L->total) *L = layout_for(n, g, rcb, true);
+    return bytes < L->total ? HACC_SR_ENOSPACE : HACC_SR_OK;
+}
+
+int ws_layout(int64_t n, const Geom& g, Layout* L, bool rcb = false) {
+    return layout_in(g_ws ? g_ws_bytes : 0, n, g, rcb, L);
 }
 
 
@@ -480,8 +501,8 @@ int hacc_sr_force_noalloc(const double* pos, const float* mass, int64_t n, doubl
     if ((rc = make_params(r_cut, eps, poly, &P)) != HACC_SR_OK) return rc;
     if (n > 0 && (!pos || !mass || !out_acc)) return HACC_SR_EINVAL;
     if (n == 0) return HACC_SR_OK;
-    const Layout L = layout_for(n, g);
-    if (L.total > kNoAllocBytes) return HACC_SR_ENOSPACE;
+    Layout L;
+    if ((rc = layout_in(kNoAllocBytes, n, g, false, &L)) != HACC_SR_OK) return rc;
     void* base = nullptr;
     if ((rc = scratch_for_current_device(&base)) != HACC_SR_OK) return rc;
     WorkspaceSwap swap(base, kNoAllocBytes);
@@ -561,8 +582,8 @@ int hacc_sr_bin(const double* pos, const float* mass, int64_t n, double box,
     if (rc != HACC_SR_OK) return rc;
     if (!cell_start) return HACC_SR_EINVAL;
     if (n > 0 && (!pos || !mass || !perm || !sorted_rec)) return HACC_SR_EINVAL;
-    const Layout L = layout_for(n, g);
-    if ((rc = check_ws(L)) != HACC_SR_OK) return rc;
+    Layout L;
+    if ((rc = ws_layout(n, g, &L)) != HACC_SR_OK) return rc;
     return timed(2, [&] {
         if (n == 0) {
             HIP_TRY(launch_fill_i32(cell_start, (int)(L.ncell + 1), 0, g_stream));
@@ -584,8 +605,8 @@ int hacc_sr_force(const double* pos, const float* mass, int64_t n, double box,
     if ((rc = make_params(r_cut, eps, poly, &P)) != HACC_SR_OK) return rc;
     if (n > 0 && (!pos || !mass || !out_acc)) return HACC_SR_EINVAL;
     if (n == 0) return HACC_SR_OK;
-    const Layout L = layout_for(n, g);
-    if ((rc = check_ws(L)) != HACC_SR_OK) return rc;
+    Layout L;
+    if ((rc = ws_layout(n, g, &L)) != HACC_SR_OK) return rc;
     int* perm = nullptr;
     if ((rc = force_into(pos, mass, n, g, P, L, out_acc, &perm)) != HACC_SR_OK) return rc;
     keep_binning(n, box, r_cut, perm);
@@ -605,9 +626,9 @@ int hacc_sr_full_step(double* pos, double* vel, const float* mass, int64_t n, do
     if (!is_fin(dt) || n_c < 1 || n_c > 1000000) return HACC_SR_EINVAL;
     if (n > 0 && (!pos || !vel || !mass || !acc_scratch)) return HACC_SR_EINVAL;
     if (n == 0) return HACC_SR_OK;
-    const Layout L = layout_for(n, g);
-    if (!g_ws || g_ws_bytes < std::max(L.total, pm_workspace_bytes(ng, n) + 256))
-        return HACC_SR_ENOSPACE;
+    Layout L;
+    if ((rc = ws_layout(n, g, &L)) != HACC_SR_OK) return rc;
+    if (g_ws_bytes < pm_workspace_bytes(ng, n) + 256) return HACC_SR_ENOSPACE;
     const int64_t m = 3 * n;
     auto pm_accel = [&] {
         return timed(7, [&] {
@@ -644,8 +665,8 @@ int hacc_sr_force_vjp(const double* pos, const float* mass, int64_t n,
     if (n > 0 && (!pos || !mass || !grad_acc || !out_grad_pos))
         return HACC_SR_EINVAL;
     if (n == 0) return HACC_SR_OK;
-    const Layout L = layout_for(n, g);
-    if ((rc = check_ws(L)) != HACC_SR_OK) return rc;
+    Layout L;
+    if ((rc = ws_layout(n, g, &L)) != HACC_SR_OK) return rc;
     int* cs = ws_at<int>(L.counts);
     float4* rec = ws_at<float4>(L.rec);
     float4* gs = ws_at<float4>(L.gsorted);
@@ -689,8 +710,8 @@ int hacc_sr_force_vjp_binned(uint64_t token, int64_t n, double box, float r_cut,
     if (token == 0 || token != g_kept.token || n != g_kept.n || box != g_kept.box ||
         r_cut != g_kept.r_cut || g_ws != g_kept.ws || g_stream != g_kept.stream)
         return HACC_SR_ESTALE;
-    const Layout L = layout_for(n, g);
-    if ((rc = check_ws(L)) != HACC_SR_OK) return rc;
+    Layout L;
+    if ((rc = ws_layout(n, g, &L)) != HACC_SR_OK) return rc;
     int* cs = ws_at<int>(L.counts);
     float4* rec = ws_at<float4>(L.rec);
     float4* gs = ws_at<float4>(L.gsorted);
@@ -733,8 +754,8 @@ int hacc_sr_rcb_bin(const double* pos, const float* mass, int64_t n, double box,
     if (n > 0 && (!pos || !mass || !perm || !sorted_rec)) return HACC_SR_EINVAL;
     const bool want_nodes = nodes || node_split || n_nodes;
     if (want_nodes && !(nodes && node_split && n_nodes)) return HACC_SR_EINVAL;
-    const Layout L = layout_for(n, g, true);
-    if ((rc = check_ws(L)) != HACC_SR_OK) return rc;
+    Layout L;
+    if ((rc = ws_layout(n, g, &L, true)) != HACC_SR_OK) return rc;
     return timed(2, [&] {
         if (n == 0) {
             HIP_TRY(launch_fill_i32(cell_start, (int)(L.ncell + 1), 0, g_stream));
@@ -786,8 +807,8 @@ int hacc_sr_force_rcb(const double* pos, const float* mass, int64_t n, double bo
     if (too_many_units(n, n)) return HACC_SR_EDOMAIN;
     if (n > 0 && (!pos || !mass || !out_acc)) return HACC_SR_EINVAL;
     if (n == 0) return HACC_SR_OK;
-    const Layout L = layout_for(n, g, true);
-    if ((rc = check_ws(L)) != HACC_SR_OK) return rc;
+    Layout L;
+    if ((rc = ws_layout(n, g, &L, true)) != HACC_SR_OK) return rc;
     int* perm = nullptr;
     const WorkItem* items;
     const int* nitems;
@@ -814,8 +835,8 @@ int hacc_sr_force_vjp_rcb(const double* pos, const float* mass, int64_t n, doubl
     if (too_many_units(n, n)) return HACC_SR_EDOMAIN;
     if (n > 0 && (!pos || !mass || !grad_acc || !out_grad_pos)) return HACC_SR_EINVAL;
     if (n == 0) return HACC_SR_OK;
-    const Layout L = layout_for(n, g, true);
-    if ((rc = check_ws(L)) != HACC_SR_OK) return rc;
+    Layout L;
+    if ((rc = ws_layout(n, g, &L, true)) != HACC_SR_OK) return rc;
     int* perm = nullptr;
     const WorkItem* items;
     const int* nitems;
@@ -841,8 +862,8 @@ int hacc_sr_force_plain(const double* pos, const float* mass, int64_t n,
     if ((rc = make_params(r_cut, eps, poly, &P)) != HACC_SR_OK) return rc;
     if (n > 0 && (!pos || !mass || !out_acc)) return HACC_SR_EINVAL;
     if (n == 0) return HACC_SR_OK;
-    const Layout L = layout_for(n, g);
-    if ((rc = check_ws(L)) != HACC_SR_OK) return rc;
+    Layout L;
+    if ((rc = ws_layout(n, g, &L)) != HACC_SR_OK) return rc;
     int* cs = ws_at<int>(L.counts);
     float4* rec = ws_at<float4>(L.rec);
     Binned bn;
@@ -869,8 +890,8 @@ int hacc_sr_force_vjp_plain(const double* pos, const float* mass, int64_t n,
     if (n > 0 && (!pos || !mass || !grad_acc || !out_grad_pos))
         return HACC_SR_EINVAL;
     if (n == 0) return HACC_SR_OK;
-    const Layout L = layout_for(n, g);
-    if ((rc = check_ws(L)) != HACC_SR_OK) return rc;
+    Layout L;
+    if ((rc = ws_layout(n, g, &L)) != HACC_SR_OK) return rc;
     int* cs = ws_at<int>(L.counts);
     float4* rec = ws_at<float4>(L.rec);
     float4* gs = ws_at<float4>(L.gsorted);
@@ -945,8 +966,8 @@ int hacc_sr_count_pairs(const double* pos, int64_t n, double box, float r_cut,
     const float zero_poly[6] = {0, 0, 0, 0, 0, 0};
     PairParams P;
     if ((rc = make_params(r_cut, eps, zero_poly, &P)) != HACC_SR_OK) return rc;
-    const Layout L = layout_for(n, g);
-    if ((rc = check_ws(L)) != HACC_SR_OK) return rc;
+    Layout L;
+    if ((rc = ws_layout(n, g, &L)) != HACC_SR_OK) return rc;
     HIP_TRY(launch_fill_i32(reinterpret_cast<int*>(out_counts), 4, 0, g_stream));
     if (n == 0) return HACC_SR_OK;
     int* cs = ws_at<int>(L.counts);

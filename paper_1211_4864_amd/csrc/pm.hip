@@ -96,14 +96,19 @@ __global__ __launch_bounds__(kPB) void k_pm_prepare(
     if (threadIdx.x == 0) mass_max[blockIdx.x] = v;
 }
 
-// Largest |mass| of all, from the blocks' maxima; kept in mass_max[kMaxBlocks]
-// for the transform.
+// The blocks' maxima of |mass|, and the largest of all, kept for the transform.
+struct MassMax {
+    const unsigned* of_block;
+    int blocks;
+    unsigned* all;
+};
+
 template <int THREADS>
-__device__ __forceinline__ double largest_mass(unsigned* mass_max, int blocks) {
+__device__ __forceinline__ double largest_mass(const MassMax& m) {
     unsigned v = 0u;
-    for (int k = threadIdx.x; k < blocks; k += THREADS) v = max(v, mass_max[k]);
+    for (int k = threadIdx.x; k < m.blocks; k += THREADS) v = max(v, m.of_block[k]);
     v = block_max<THREADS>(v);
-    if (blockIdx.x == 0 && threadIdx.x == 0) mass_max[kMaxBlocks] = v;
+    if (blockIdx.x == 0 && threadIdx.x == 0) *m.all = v;
     return (double)__uint_as_float(v);
 }
 
@@ -211,15 +216,14 @@ constexpr int kRow = 1 << kRowBits;
 
 __global__ __launch_bounds__(kDB) void k_pm_deposit_direct(
     const double* __restrict__ pos, const float* __restrict__ mass, int n, int ng,
-    double inv_d, unsigned* __restrict__ mass_max, int mass_blocks,
-    unsigned long long* __restrict__ grid) {
+    double inv_d, MassMax mass_max, unsigned long long* __restrict__ grid) {
     __shared__ int owner[kTable];
     __shared__ unsigned long long sum[kTable];
     for (int v = threadIdx.x; v < kTable; v += kDB) {
         owner[v] = -1;
         sum[v] = 0ull;
     }
-    const double mmax = largest_mass<kDB>(mass_max, mass_blocks);   // synchronises
+    const double mmax = largest_mass<kDB>(mass_max);   // synchronises
     if (!(mmax > 0.0)) return;                       // uniform: nothing to deposit
     const double scale = kFixedScale / ((double)n * mmax);
     const int first = blockIdx.x * kDChunk;
@@ -338,8 +342,7 @@ __device__ __forceinline__ int64_t tile_corner_index(const int t0[3], int v, int
 // the deposit alone takes 0.78 ms.
 __global__ __launch_bounds__(kPB) void k_pm_deposit(
     const int* __restrict__ keys, const int* __restrict__ vals,
-    const float4* __restrict__ rec_in, float4* rec, int n, int ng,
-    unsigned* __restrict__ mass_max, int mass_blocks,
+    const float4* __restrict__ rec_in, float4* rec, int n, int ng, MassMax mass_max,
     unsigned long long* __restrict__ grid) {
     __shared__ Ranges r;
     __shared__ unsigned long long acc[kCorners];
@@ -360,7 +363,7 @@ __global__ __launch_bounds__(kPB) void k_pm_deposit(
             if (q < m) rec[first + q] = p[j];
         }
     }
-    const double mmax = largest_mass<kPB>(mass_max, mass_blocks);
+    const double mmax = largest_mass<kPB>(mass_max);
     if (!(mmax > 0.0)) return;                       // uniform: nothing to deposit
     const double scale = kFixedScale / ((double)n * mmax);
     find_ranges(keys, first, m, r);                  // also: the block's records are written
@@ -763,7 +766,7 @@ bool direct_pm(int ng, int64_t n) {
 }
 
 struct PmLayout {
-    size_t a, b, tw, sym, mmax, keys_a, vals_a, keys_b, vals_b, rec_in, rec, hist, scan_tmp,
+    size_t a, b, tw, sym, mmax, block_max, keys_a, vals_a, keys_b, vals_b, rec_in, rec, hist, scan_tmp,
         total;
 };
 
@@ -785,7 +788,7 @@ PmLayout pm_layout(int ng, int64_t n) {
     L.b = take(cells * sizeof(float2));      // also the fixed-point deposit
     L.tw = take((size_t)ng * sizeof(float2));
     L.sym = take((size_t)ng * sizeof(float4));
-    L.mmax = take(sizeof(unsigned) * (kMaxBlocks + 1));
+    L.mmax = take(sizeof(unsigned));
     L.keys_a = take(ni);
     L.vals_a = take(ni);
     L.keys_b = take(ni);
@@ -793,7 +796,13 @@ PmLayout pm_layout(int ng, int64_t n) {
     L.rec_in = take(sizeof(float4) * (size_t)nn);
     L.rec = take(sizeof(float4) * (size_t)nn);
     L.hist = take(sizeof(int) * hist_n);
-    L.scan_tmp = take(sizeof(int) * scan_tmp_ints((int)hist_n));
+    // until the transform writes it, grid a holds the blocks' maxima and, where
+    // there is room for them, the scan's sums
+    static_assert(sizeof(unsigned) * kMaxBlocks <= 8 * 8 * 8 * sizeof(float2), "fits 8^3");
+    L.block_max = L.a;
+    L.scan_tmp = L.a + sizeof(unsigned) * kMaxBlocks;
+    const size_t tmp = sizeof(int) * scan_tmp_ints((int)hist_n);
+    if (L.scan_tmp + tmp > L.b) L.scan_tmp = take(tmp);
     L.total = off;
     return L;
 }
@@ -814,6 +823,7 @@ hipError_t launch_pm_accel(const double* pos, const float* mass, int n, double b
     float2* tw = reinterpret_cast<float2*>(base + PL.tw);
     float4* sym = reinterpret_cast<float4*>(base + PL.sym);
     unsigned* mmax = reinterpret_cast<unsigned*>(base + PL.mmax);
+    unsigned* block_maxima = reinterpret_cast<unsigned*>(base + PL.block_max);
     int* ka = reinterpret_cast<int*>(base + PL.keys_a);
     int* va = reinterpret_cast<int*>(base + PL.vals_a);
     int* kb = reinterpret_cast<int*>(base + PL.keys_b);
@@ -826,11 +836,12 @@ hipError_t launch_pm_accel(const double* pos, const float* mass, int n, double b
     const double inv_d = (double)ng / box;
     const int mb = std::min(kMaxBlocks, std::max(blocks_for(n, kPB), blocks_for(cells / 2, kPB)));
     hipLaunchKernelGGL(k_pm_prepare, dim3(mb), dim3(kPB), 0, st, mass, n, ng, (float)d,
-                       reinterpret_cast<ulonglong2*>(Q), tw, sym, mmax);
+                       reinterpret_cast<ulonglong2*>(Q), tw, sym, block_maxima);
+    const MassMax mass_max{block_maxima, mb, mmax};
     const bool direct = direct_pm(ng, n);
     if (direct) {
         hipLaunchKernelGGL(k_pm_deposit_direct, dim3(blocks_for(n, kDChunk)), dim3(kDB), 0, st, pos,
-                           mass, n, ng, inv_d, mmax, mb, Q);
+                           mass, n, ng, inv_d, mass_max, Q);
     } else {
         hipLaunchKernelGGL(k_pm_keys, dim3(blocks_for(n, kPB)), dim3(kPB), 0, st, pos, mass,
                            n, ng, inv_d, ka, rec_in);
@@ -849,7 +860,7 @@ hipError_t launch_pm_accel(const double* pos, const float* mass, int n, double b
         }
         hipLaunchKernelGGL(k_pm_deposit, dim3(blocks_for(n, kChunk)), dim3(kPB), 0, st,
                            (const int*)ka, (const int*)va, (const float4*)rec_in, rec, n, ng,
-                           mmax, mb, Q);
+                           mass_max, Q);
     }
     FftArgs fa{};
     fa.a = A;
@@ -857,7 +868,7 @@ hipError_t launch_pm_accel(const double* pos, const float* mass, int n, double b
     fa.q = Q;
     fa.tw = tw;
     fa.sym = sym;
-    fa.mmax_bits = mmax + kMaxBlocks;
+    fa.mmax_bits = mmax;
     // density = q (n max|m| / 2^62) / D^3; k_fft multiplies by max|m|
     fa.unit = (double)n / 4611686018427387904.0 / (d * d * d);
     fa.d = (float)d;
