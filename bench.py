@@ -304,15 +304,35 @@ def rcb_leg(hsr, torch, w, pos, mass, g_np, inside, leaf_max, launches=2):
 PM_GRID = {"cfg1": 128, "cfg2": 128, "cfg4": 128, "cfg3": 256, "cfg3s": 256, "cfg5": 512}
 
 
+def pm_bytes(n: int, ng: int) -> dict:
+    """Bytes that the kernels of a PM solve read and write, each array once per
+    kernel, by the path that n and ng take (csrc/pm.hip, direct_pm and
+    pm_sort_shape).  Atomic traffic and what a kernel reads again are not
+    counted.
+
+    Per grid cell 144: clearing the fixed-point grid 8; forward z pass 16, y
+    pass 16; the fused x pass reads 8 and writes two grids 16; inverse y and z
+    passes over two grids 32 each; interpolation reads two grids 16.
+    Per particle, in input order 68: mass maximum 4; deposit 28 (position,
+    mass); interpolation 36 (position, acceleration).  Sorted: mass maximum 4;
+    keys 48 (position, mass, key, record); per radix pass 20 (key twice, index,
+    key, index; the first reads no index), on 8^3, which has one tile and none,
+    the indices 4; deposit 40 (key, index, record read and written);
+    interpolation 36 (key, index, record, acceleration)."""
+    if n <= (1 << 17) + min(ng ** 3 // 64, 1 << 18):
+        path, per = "input order", 68
+    else:
+        bits = 3 * (ng.bit_length() - 1 - 3)
+        passes = (bits + 8) // 9
+        path = f"{passes} radix passes"
+        per = 4 + 48 + (20 * passes - 4 if passes else 4) + 40 + 36
+    return {"path": path, "bytes_per_particle": per, "bytes": 144.0 * ng ** 3 + per * float(n)}
+
+
 def pm_leg(hsr, torch, w, pos, mass, ng, launches=3):
     """The long-range PM solve (Sec. II) on the workload's own PM grid (the
     grid whose 3 cells are r_cut): time per solve and its HBM rate against
-    the algorithmic bytes of its passes: per grid cell 144 B (clearing the
-    fixed-point grid 8; forward z pass 16, y pass 16; the fused x pass reads
-    8 and writes two grids 16; inverse y and z passes over two grids 32
-    each; interpolation reads two grids 16), per particle 172 B (mass
-    maximum 4; cell keys 32; three radix passes 60; deposit 36;
-    interpolation 40).  Atomic traffic is not counted."""
+    the bytes that its passes move (pm_bytes)."""
     if w.box <= 0:
         return None
     acc = hsr.pm_accel(pos, mass, w.box, ng)
@@ -324,9 +344,10 @@ def pm_leg(hsr, torch, w, pos, mass, ng, launches=3):
     n_p, ms_p = hsr.timing_read(hsr.TIMER_PM)
     hsr.timing_enable(False)
     ms = ms_p / max(n_p, 1)
-    algo = 144.0 * ng ** 3 + 172.0 * w.n
+    moved = pm_bytes(w.n, ng)
+    algo = moved["bytes"]
     return {"ng": ng, "ms_per_solve": round(ms, 4),
-            "algorithmic_bytes": algo,
+            "path": moved["path"], "algorithmic_bytes": algo,
             "roofline": {"bound": "hbm", "achieved": round(algo / (ms * 1e-3) / 1e9, 1),
                          "peak": 8000.0, "unit": "GB/s",
                          "frac": round(algo / (ms * 1e-3) / 8e12, 4)}}
