@@ -259,7 +259,7 @@ int hacc_sr_force_vjp_plain(const double *pos, const float *mass, int64_t n,
  * sums in fixed point, so results are bitwise reproducible.  Uses the
  * workspace (size from hacc_sr_pm_workspace_bytes for the same ng and n:
  * two complex ng^3 grids and the buffers of a sort of the n particles by
- * grid cell); n < 2^31 - 1.
+ * tiles of grid cells); n < 2^31 - 1.
  */
 int hacc_sr_pm_workspace_bytes(int32_t ng, int64_t n, size_t *bytes);
 int hacc_sr_pm_accel(const double *pos, const float *mass, int64_t n, double box,
@@ -319,7 +319,11 @@ int hacc_sr_count_pairs(const double *pos, int64_t n, double box, float r_cut,
  * launch of a pair kernel.  kernel: 0 = forward pair kernel, 1 = VJP pair
  * kernel, 2 = binning (all its kernels), 3 = work-list build, 4 = plain
  * forward kernel, 5 = plain VJP kernel, 6 = RCB tree and leaf table,
- * 7 = long-range PM solve (hacc_sr_pm_accel).
+ * 7 = long-range PM solve (hacc_sr_pm_accel).  Where a chaining-mesh force,
+ * VJP or full step bins at most 2^19 particles, the first part of the work list
+ * (windows, pair work, histogram of the items) runs inside the binning's
+ * launches and counts under 2; 3 is then the rest of it, the writing of the
+ * items.
  * hacc_sr_timing_enable(1) starts recording (and clears earlier records);
  * hacc_sr_timing_read waits for the recorded events and returns the number
  * of launches and their summed duration in milliseconds.

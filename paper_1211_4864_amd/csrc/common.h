@@ -91,9 +91,13 @@ struct WorkBuffers {
 hipError_t launch_cell_keys(const double* pos, const float* mass, int n,
                             Geom g, int* keys, float4* rec, hipStream_t st);
 // Largest set of the counting sort (launch_counting_sort), which beats the
-// radix passes there: binning 512000 NFW particles takes 106 us against 139,
-// 262144 72 / 129, 32768 46 / 68, 1000 20 / 49; at 1030301 it is 185 / 160
-// (random single-entry atomics and writes).
+// radix passes there.  Binning, this sort / radix passes in us, uniform and
+// Plummer sets at a particle per mesh cell: 1000 16 / 33 and 31 / 33, 32768
+// 23 / 46 and 32 / 48, 262144 47 / 79 and 55 / 80, 524288 75 / 88 and 88 / 90,
+// 700000 93 / 94 and 108 / 95, 1030301 144 / 105 and 153 / 106 (random
+// single-entry atomics and writes).  Concentrated sets: all on one point 65536
+// 38 / 75, 524288 99 / 91; ten clumps inside cells 262144 77 / 84, 524288
+// 127 / 94, and where a bucket is 64 sort keys 297 / 102 (100^3 cells).
 constexpr int kCountingParticles = 1 << 19;
 // Sets whose work list is a single one in decreasing cost; larger ones have
 // one per XCD.

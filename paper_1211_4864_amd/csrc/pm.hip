@@ -112,7 +112,7 @@ __device__ __forceinline__ double largest_mass(const MassMax& m) {
     return (double)__uint_as_float(v);
 }
 
-// ---- sort by cell
+// ---- sort by tile
 
 // Lower grid index and the CIC fraction of a coordinate (grid point g at
 // g D, periodic).
@@ -758,9 +758,12 @@ void pm_sort_shape(int ng, int* passes, int* digit_bits) {
 
 // Whether to deposit and interpolate in input order, without the sort: its
 // launches cost more than the scattered accesses to a grid (microseconds,
-// direct / sorted, NFW): 32^3 with 32768 particles 42 / 76, with 262144
-// 135 / 73; 64^3 50000 60 / 101, 262144 163 / 101; 128^3 16384 91 / 171,
-// 262144 238 / 186; 256^3 262144 530 / 555, 2097152 1427 / 937.
+// direct / sorted, Plummer): 8^3 with 2048 particles 23 / 33, 131072 36 / 45;
+// 16^3 16384 30 / 54, 131072 50 / 59; 32^3 32768 40 / 74, 131072 64 / 69,
+// 200000 95 / 70; 64^3 65536 61 / 97, 131072 90 / 97, 262144 133 / 97; 128^3
+// 131072 132 / 173, 262144 176 / 191, 524288 272 / 222; 256^3 393216 560 / 598,
+// 1048576 825 / 799; 512^3 393216 5787 / 5865, 4194304 7448 / 7304.  Uniform
+// sets and all particles on one point cross over later.
 bool direct_pm(int ng, int64_t n) {
     return n <= (1 << 17) + std::min<int64_t>((int64_t)ng * ng * ng / 64, 1 << 18);
 }

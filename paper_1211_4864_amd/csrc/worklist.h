@@ -128,7 +128,7 @@ __device__ __forceinline__ int cost_bucket(int sources, int ksplit) {
 // Per cell: its window size; per column (cx, cy): its pair work; in all: the
 // pair work.  One wave takes a column (coalesced along z: a neighbour column
 // gives a cell at most two ranges of the sorted entries).
-// Block `block` of `blocks`, each of kWorkWorkBlock threads.
+// Block `block` of `blocks`, each of kWorkBlock threads.
 __device__ __forceinline__ void windows_block(
     const int* __restrict__ cs, const Geom& g, int* __restrict__ cell_window,
     unsigned long long* __restrict__ col_cost, WorkControl* __restrict__ ctl, int block,

@@ -25,12 +25,15 @@
 // list follow at the end in plain decreasing cost.  A set small enough for
 // every L2 (kOneListParticles) takes one list in decreasing cost.
 //
-// Launches: units' windows and cost; the columns' XCDs (8 lists only); the
-// histogram of the items over (list, cost) buckets; the items themselves,
-// each block expanding its units' items in parallel straight into their final
-// slots.  Latency-bound integer passes over the cells; three launches replace
-// nine (a scan, a separate item array and a one-thread bucket scan among
-// them: 1003 particles 47 -> 16 us).
+// Launches: the control words' clearing; units' windows and cost; the columns'
+// XCDs (8 lists only); the histogram of the items over (list, cost) buckets; the
+// items themselves, each block expanding its units' items in parallel straight
+// into their final slots.  Five with 8 lists, four with one (RCB leaves of small
+// sets); after a counting sort only the last is left, the others run beside the
+// sort's kernels and in its clearing.  Latency-bound integer passes over the
+// cells; twelve launches before (three fills, a scan in three, a separate
+// item array and a one-thread bucket scan among them: 1003 particles 47 -> 16 us
+// without the sharing).
 //
 // This replaces the tree walk that gathers leaf interaction lists in the
 // paper's BG/Q code (Habib et al. 2012, Sec. III, walk minimisation and the
