@@ -85,7 +85,7 @@ constexpr int kCountTable = 1 << kCountTableBits;
 // kCountBlock first counts a block's particles per bucket in an LDS table (open
 // addressing; it always has a free slot) and adds once per bucket and block,
 // 2048 times at most instead of 524288 (all on one point: 13 ms of adds; the
-// whole sort takes 0.09 now).  Also clears zero[i] where zero is given.
+// whole sort takes 0.065 now).  Also clears zero[i] where zero is given.
 template <int COUNTS>
 __global__ __launch_bounds__(kBlock) void k_cell_keys(
     const double* __restrict__ pos, const float* __restrict__ mass, int n,
@@ -493,10 +493,10 @@ __global__ __launch_bounds__(kBlock) void k_radix_scatter_staged(
 // those counts added up per segment of the input, so that a particle's place
 // is the keys below its own, its key's counts in the segments before, and the
 // equal keys before it in its own segment.  All of it linear in n: with 524288
-// particles on one point the sort takes 92 us (22.5 ms counted one by one, 190
-// by radix passes), with 65536 38 (1704, 94), with a tenth of 524288 there 112
-// (1567, 118); 524288 in a few cells of 100^3, where a bucket is 64 keys,
-// 300 (3165, 170).
+// particles on one point the sort takes 65 us (22.5 ms counted one by one, 91
+// by radix passes), with 65536 26 (1704, 74), with a tenth of 524288 there 86
+// (1567, 94); 524288 in a few cells of 100^3, where a bucket is 64 keys,
+// 304 (3165, 102).
 
 // Entry of the order array: the key bits below the bucket, then the index.
 constexpr unsigned kIndexMask = (1u << kCountingIndexBits) - 1u;
@@ -509,8 +509,9 @@ constexpr unsigned kIndexMask = (1u << kCountingIndexBits) - 1u;
 // whose counts fit into the bucket's entries.  A block of a longer segment
 // searches the keys of those before it.
 // Where it lies: counting one by one takes 1 us per 64 entries of the bucket in
-// each of its waves, in turn; counting per segment 11 us, and 2.5 more per
-// block that is searched, which buckets of 64 keys need sooner.
+// each of its waves, in turn; counting per segment 3 us where a wave has few
+// keys of heavy buckets and up to 30 where it has 64, and 2.5 more per block
+// that is searched, which buckets of 64 keys need sooner.
 constexpr int kHeavyLeast = 1024, kHeavyLeast64 = 2048;
 constexpr int kLongestSegBits = 12;      // a segment's count fits 16 bits
 
@@ -547,21 +548,58 @@ struct BesideWork {
     int first;
 };
 
-// Equal sort keys among the block's kBlock keys in `sk`: all of them, those of
-// lower index, and the first one's index.
+// The equal sort keys in a block, for its lanes with `in`: all of them, those
+// of lower index, and where the first one is.  Each wave lists its keys with
+// their numbers, a key in turn; its first lane of a key looks that key up in the
+// other waves' lists.  Whole block.
 struct Equal {
     int all, before, first;
 };
 
-__device__ __forceinline__ Equal equal_keys(const int* sk, int key) {
-    Equal q{0, 0, kBlock};
-    for (int j = 0; j < kBlock; ++j) {
-        const bool same = sk[j] == key;
-        q.all += same;
-        q.before += same && j < (int)threadIdx.x;
-        if (same && q.first == kBlock) q.first = j;
+struct KeyLists {
+    int key[kBlock / kWave][kWave];
+    int count[kBlock / kWave][kWave];
+    int lane[kBlock / kWave][kWave];     // the wave's first of that key
+    int len[kBlock / kWave];
+};
+
+__device__ __forceinline__ Equal equal_keys(KeyLists& s, int key, bool in) {
+    constexpr int kW = kBlock / kWave;
+    const int lane = lane_id(), w = (int)threadIdx.x / kWave;
+    int lead = lane, same = 0, before = 0, len = 0;
+    for (uint64_t left = __ballot(in); left; ++len) {
+        const int l = __ffsll((unsigned long long)left) - 1;
+        const int k = __shfl(key, l);
+        const uint64_t m = __ballot(in && key == k);
+        if (in && key == k) {
+            lead = l;
+            same = __popcll(m);
+            before = __popcll(m & lanemask_lt());
+        }
+        if (lane == l) {
+            s.key[w][len] = k;
+            s.count[w][len] = same;
+            s.lane[w][len] = l;
+        }
+        left &= ~m;
     }
-    return q;
+    if (lane == 0) s.len[w] = len;
+    __syncthreads();
+    int all = same, lower = 0, first = w * kWave + lane;
+    if (in && before == 0) {
+        for (int v = kW - 1; v >= 0; --v) {
+            if (v == w) continue;
+            for (int j = 0; j < s.len[v]; ++j) {
+                if (s.key[v][j] != key) continue;
+                all += s.count[v][j];
+                if (v < w) {
+                    lower += s.count[v][j];
+                    first = v * kWave + s.lane[v][j];
+                }
+            }
+        }
+    }
+    return Equal{__shfl(all, lead), before + __shfl(lower, lead), __shfl(first, lead)};
 }
 
 __global__ __launch_bounds__(kBlock) void k_place(
@@ -583,12 +621,9 @@ __global__ __launch_bounds__(kBlock) void k_place(
     const bool is_heavy = any && count >= heavy;
     if (live && !is_heavy) order[b + arrival[i]] = (low << kCountingIndexBits) | (unsigned)i;
     if (!any || !__syncthreads_or(is_heavy)) return;
-    __shared__ int sk[kBlock];
-    sk[threadIdx.x] = key;
-    __syncthreads();
-    if (!is_heavy) return;
-    const Equal q = equal_keys(sk, key);
-    if (q.before) return;
+    __shared__ KeyLists lists;
+    const Equal q = equal_keys(lists, key, is_heavy);
+    if (!is_heavy || q.before) return;
     const int bits = heavy_seg_bits(n, drop, count);
     const int seg = i >> bits;
     if (drop) atomicAdd(&order[b + low], (unsigned)q.all);
@@ -602,6 +637,7 @@ __device__ __forceinline__ void gather_heavy(
     const int* __restrict__ keys, int n, int drop, int heavy,
     const float4* __restrict__ rec_in, float4* __restrict__ rec, int* __restrict__ perm,
     int* __restrict__ keys_out) {
+    __shared__ KeyLists lists;
     __shared__ int sk[kBlock];
     __shared__ int base[kBlock];        // by the first particle of a key
     __shared__ int longest;             // bits of the block's longest segment
@@ -612,25 +648,24 @@ __device__ __forceinline__ void gather_heavy(
     const int count = live ? start[(key >> drop) + 1] - b : 0;
     const bool is_heavy = count >= heavy;
     if (threadIdx.x == 0) longest = 0;
-    sk[threadIdx.x] = key;
     if (!__syncthreads_or(is_heavy)) return;
-    Equal q{0, 0, kBlock};
+    Equal q = equal_keys(lists, key, is_heavy);
     int bits = 0;
     if (is_heavy) {
-        q = equal_keys(sk, key);
         bits = heavy_seg_bits(n, drop, count);
         atomicMax(&longest, bits);
     }
-    // the counts before each key's first particle, added up by 16 lanes
-    constexpr int kGroup = 16;
+    // the counts before each key's first particle, added up by 16 lanes, or by
+    // the whole wave where it has one
     const int low = key & ((1 << drop) - 1);
     const int seg = i >> bits;
     const int lane = lane_id(), wave0 = (int)threadIdx.x - lane;
     for (uint64_t left = __ballot(is_heavy && q.before == 0); left;) {
+        const int group = left & (left - 1) ? 16 : kWave;
         uint64_t mine = left;                       // the group's: first to fourth left
 #pragma unroll
-        for (int t = 0; t < kWave / kGroup; ++t) {
-            if (t < lane / kGroup) mine &= mine - 1;
+        for (int t = 0; t < kWave / 16; ++t) {
+            if (t < lane / group) mine &= mine - 1;
             left &= left - 1;
         }
         const int l = mine ? __ffsll((unsigned long long)mine) - 1 : 0;
@@ -639,16 +674,15 @@ __device__ __forceinline__ void gather_heavy(
         const unsigned* row = area + (1 << drop) + lw * heavy_row(n, __shfl(bits, l));
         unsigned sum = 0u;
         if (mine) {
-            for (int v = lane % kGroup; v < lw; v += kGroup) sum += area[v];
+            for (int v = lane & (group - 1); v < lw; v += group) sum += area[v];
 #pragma unroll 8
-            for (int w = lane % kGroup; w <= sg >> 1; w += kGroup) {
+            for (int w = lane & (group - 1); w <= sg >> 1; w += group) {
                 const unsigned two = row[w];
                 sum += (2 * w < sg ? two & 0xffffu : 0u) + (2 * w + 1 < sg ? two >> 16 : 0u);
             }
         }
-#pragma unroll
-        for (int o = 1; o < kGroup; o <<= 1) sum += (unsigned)__shfl_xor((int)sum, o);
-        if (mine && lane % kGroup == 0) base[wave0 + l] = (int)sum;
+        for (int o = 1; o < group; o <<= 1) sum += (unsigned)__shfl_xor((int)sum, o);
+        if (mine && (lane & (group - 1)) == 0) base[wave0 + l] = (int)sum;
     }
     __syncthreads();
     // the equal keys in the blocks before this one in its segment
@@ -680,7 +714,7 @@ __global__ __launch_bounds__(kBlock) void k_order_gather(
                          w_list.b.ctl, blockIdx.x - w_list.first);
         return;
     }
-    if (n >= heavy && *any_heavy)              // uniform
+    if (n >= heavy && *any_heavy)                    // uniform
         gather_heavy(order, start, keys, n, drop, heavy, rec_in, rec, perm, keys_out);
     __shared__ __align__(16) unsigned entries[kBlock / kWave][kWave];
     const int k = blockIdx.x * kBlock + threadIdx.x;

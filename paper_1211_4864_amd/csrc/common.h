@@ -96,8 +96,8 @@ hipError_t launch_cell_keys(const double* pos, const float* mass, int n,
 // 23 / 46 and 32 / 48, 262144 47 / 79 and 55 / 80, 524288 75 / 88 and 88 / 90,
 // 700000 93 / 94 and 108 / 95, 1030301 144 / 105 and 153 / 106 (random
 // single-entry atomics and writes).  Concentrated sets: all on one point 65536
-// 38 / 75, 524288 99 / 91; ten clumps inside cells 262144 77 / 84, 524288
-// 127 / 94, and where a bucket is 64 sort keys 297 / 102 (100^3 cells).
+// 26 / 74, 524288 65 / 91; ten clumps inside cells 262144 79 / 84, 524288
+// 127 / 94, and where a bucket is 64 sort keys 304 / 102 (100^3 cells).
 constexpr int kCountingParticles = 1 << 19;
 // Sets whose work list is a single one in decreasing cost; larger ones have
 // one per XCD.
