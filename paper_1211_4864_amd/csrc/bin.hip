@@ -631,9 +631,9 @@ __global__ __launch_bounds__(kBlock) void k_place(
               (unsigned)q.all << (16 * (seg & 1)));
 }
 
-// The block's particles of heavy buckets, by input index.
+// Block `block` of the input's particles: those of heavy buckets, by input index.
 __device__ __forceinline__ void gather_heavy(
-    const unsigned* __restrict__ order, const int* __restrict__ start,
+    int block, const unsigned* __restrict__ order, const int* __restrict__ start,
     const int* __restrict__ keys, int n, int drop, int heavy,
     const float4* __restrict__ rec_in, float4* __restrict__ rec, int* __restrict__ perm,
     int* __restrict__ keys_out) {
@@ -641,7 +641,7 @@ __device__ __forceinline__ void gather_heavy(
     __shared__ int sk[kBlock];
     __shared__ int base[kBlock];        // by the first particle of a key
     __shared__ int longest;             // bits of the block's longest segment
-    const int i0 = blockIdx.x * kBlock, i = i0 + (int)threadIdx.x;
+    const int i0 = block * kBlock, i = i0 + (int)threadIdx.x;
     const bool live = i < n;
     const int key = live ? keys[i] : -1;
     const int b = live ? start[key >> drop] : 0;
@@ -702,10 +702,13 @@ __device__ __forceinline__ void gather_heavy(
 
 // A wave takes 64 consecutive entries.  Their buckets' entries are read 64 at
 // a time, coalesced, and handed round through LDS as broadcast uint4 reads;
-// two instructions per entry where the wave lies in one bucket.
+// two instructions per entry where the wave lies in one bucket.  The heavy
+// buckets' particles have the first `heavy_blocks` blocks (one per block of the
+// input where the set is large enough for one): beside the others, so that
+// these need not wait for the flag (32768 particles: 5.2 us against 6.8).
 __global__ __launch_bounds__(kBlock) void k_order_gather(
     const unsigned* __restrict__ order, const int* __restrict__ start,
-    const int* __restrict__ keys, int n, int drop, int heavy,
+    const int* __restrict__ keys, int n, int drop, int heavy, int heavy_blocks,
     const int* __restrict__ any_heavy, const float4* __restrict__ rec_in,
     float4* __restrict__ rec, int* __restrict__ perm, int* __restrict__ keys_out,
     BesideWork w_list) {
@@ -714,10 +717,14 @@ __global__ __launch_bounds__(kBlock) void k_order_gather(
                          w_list.b.ctl, blockIdx.x - w_list.first);
         return;
     }
-    if (n >= heavy && *any_heavy)                    // uniform
-        gather_heavy(order, start, keys, n, drop, heavy, rec_in, rec, perm, keys_out);
+    if ((int)blockIdx.x < heavy_blocks) {
+        if (*any_heavy)
+            gather_heavy(blockIdx.x, order, start, keys, n, drop, heavy, rec_in, rec, perm,
+                         keys_out);
+        return;
+    }
     __shared__ __align__(16) unsigned entries[kBlock / kWave][kWave];
-    const int k = blockIdx.x * kBlock + threadIdx.x;
+    const int k = ((int)blockIdx.x - heavy_blocks) * kBlock + threadIdx.x;
     const int lane = lane_id(), w = threadIdx.x / kWave;
     if (k - lane >= n) return;
     const unsigned mine = k < n ? order[k] : 0u;
@@ -942,14 +949,17 @@ hipError_t launch_counting_sort(const double* pos, const float* mass, int n, Geo
                                   buckets == cell_start ? nullptr : cell_start, sub,
                                   n >= heavy ? any_heavy : nullptr, heavy, st);
     if (e != hipSuccess) return e;
-    const BesideWork beside{CellUnits{cell_start, g}, work ? *work : WorkBuffers{}, nb};
+    const int hb = n >= heavy ? nb : 0;
+    const CellUnits cells{cell_start, g};
+    const WorkBuffers bufs = work ? *work : WorkBuffers{};
     hipLaunchKernelGGL(k_place, dim3(nb + (work ? window_blocks(g.N) : 0)), dim3(kBlock), 0, st,
                        (const int*)keys, (const int*)arrival, (const int*)buckets, n, drop,
-                       heavy, order, (const int*)any_heavy, beside);
-    hipLaunchKernelGGL(k_order_gather, dim3(nb + (work ? blocks_for(ncell, kBlock) : 0)),
+                       heavy, order, (const int*)any_heavy, BesideWork{cells, bufs, nb});
+    hipLaunchKernelGGL(k_order_gather, dim3(hb + nb + (work ? blocks_for(ncell, kBlock) : 0)),
                        dim3(kBlock), 0, st, (const unsigned*)order, (const int*)buckets,
-                       (const int*)keys, n, drop, heavy, (const int*)any_heavy,
-                       (const float4*)rec_in, rec, perm, keys_out, beside);
+                       (const int*)keys, n, drop, heavy, hb, (const int*)any_heavy,
+                       (const float4*)rec_in, rec, perm, keys_out,
+                       BesideWork{cells, bufs, hb + nb});
     return hipGetLastError();
 }
 

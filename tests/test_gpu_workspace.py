@@ -107,3 +107,32 @@ def test_pm_workspace(cuda, ng, n):
     assert _call(lib, cuda, "hacc_sr_pm_accel", size, _ptr(p), _ptr(m), n, 1.0, ng,
                  ctypes.c_float(0.8), 3, _ptr(out)) == 0
     assert torch.equal(ref, out)
+
+
+def test_kept_binning_in_a_smaller_workspace(cuda):
+    """The VJP on the force's own binning, whose work list lies where the sort's
+    buffers were, in the usual workspace and in one without the finer counters."""
+    lib = hsr.load()
+    n, cells, box = 65536, 16, 1.0
+    r_cut = float(np.float32(0.9999 / cells))
+    fit = fit_fgrid(r_cut / 3, 3.0, 0.164)
+    rng = np.random.default_rng(9)
+    p = torch.from_numpy(rng.random((n, 3))).to(cuda)
+    m = torch.from_numpy(rng.random(n).astype(np.float32)).to(cuda)
+    g = torch.from_numpy(cotangent(n, 4)).to(cuda)
+    sr = (n, box, ctypes.c_float(r_cut), ctypes.c_float(fit.eps), _lib.poly_array(fit.coeffs))
+    ref = hsr.force_vjp(p, m, box, r_cut, fit.eps, fit.coeffs, g)
+    for size in (hsr.workspace_bytes(n, box, r_cut), _without_sub_cells(n, cells)):
+        ws = torch.empty(size, dtype=torch.uint8, device=cuda)
+        stream = torch.cuda.current_stream(cuda).cuda_stream
+        _lib.check(lib.hacc_sr_set_stream(ctypes.c_void_p(stream)))
+        _lib.check(lib.hacc_sr_set_workspace(_ptr(ws), size))
+        acc = torch.empty((n, 3), dtype=torch.float32, device=cuda)
+        grad = torch.full((n, 3), float("nan"), dtype=torch.float64, device=cuda)
+        assert lib.hacc_sr_force(_ptr(p), _ptr(m), *sr, _ptr(acc)) == 0
+        token = ctypes.c_uint64(0)
+        assert lib.hacc_sr_binning_token(ctypes.byref(token)) == 0 and token.value
+        assert lib.hacc_sr_force_vjp_binned(token, *sr, _ptr(g), _ptr(grad)) == 0
+        torch.cuda.synchronize()
+        _lib.check(lib.hacc_sr_set_workspace(None, 0))
+        assert torch.equal(grad, ref)
